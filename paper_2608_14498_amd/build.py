@@ -24,7 +24,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIBDIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIBDIR, "librollplex.so")
-SOURCES = ["api.cpp", "elementwise.hip", "gemm.hip", "attention.hip", "calibrate.hip"]
+SOURCES = ["api.cpp", "elementwise.hip", "gemm.hip", "gemm_flex.hip", "attention.hip", "calibrate.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
