@@ -15,7 +15,7 @@
 // the score registers, converted to bf16, directly as the B operand.  K/V tile loads
 // for tile t+1 are in flight while tile t is computed (double-buffered LDS).
 //
-// fp32: one thread per query, K/V tiles in LDS, exact fp32 math.
+// fp32: the same tiles on the fp32 matrix cores, keys split over the waves of a workgroup.
 //
 // decode: split-KV over 256-key chunks, all q heads of a kv head per workgroup,
 // then a merge over chunks.
@@ -424,63 +424,182 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------
-// fp32 attention: one thread per query, 64-key tiles in LDS, exact fp32 arithmetic.
+// fp32 attention on the fp32 matrix cores (v_mfma_f32_32x32x2: exact fp32 products).
+// A workgroup owns 32 queries of one head; its NW waves take the 32-key tiles in turn and
+// their (max, sum, o) are combined in LDS, so that also the few hundred queries of a small
+// fp32 model fill the chip.  Per tile S^T = K Q^T (lane l holds query l % 32 and the head
+// dimensions 8 j + 4 (l / 32) + 0..3, the same for K and Q: 16-byte loads straight from
+// global memory), then O^T += V^T P^T with the scores as they are: score register e belongs
+// to keys 8 (e/4) + e%4 (+ 4 in the upper half wave), which is the k pair of MFMA e.  The V
+// values of a tile and the K rows of the wave's next one are in flight under the score
+// MFMAs.  Bound by load latency at these sizes (2 x 512 queries, 4 heads of 64, launch and
+// timing events included: 23 us a layer, where one thread per query walked the keys in 685;
+// 2 x 64 queries over 512 + 64 keys: 24, from 784).  A split by tile index alone: a sequence's result does not depend on the batch.
 // ------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void k_attn_f32(SeqTable st, AttnArgs a) {
-  constexpr int BQ = 64, KT = 64;
-  __shared__ float Ksh[KT][D];
-  __shared__ float Vsh[KT][D];
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64) void k_attn_f32(SeqTable st, AttnArgs a) {
+  constexpr int BQ = 32, KT = 32, NC = D / 8, DB = D / 32;
+  __shared__ float4 part[NW][DB * 4][64];  // unnormalised o of each wave: [quad][lane]
+  __shared__ float2 ml[NW][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 31, fk = lane >> 5;
   const int h = blockIdx.x % a.Hq;
-  const QBlock qb = find_qblock(st, blockIdx.x / a.Hq, BQ);
+  QBlock qb = find_qblock(st, blockIdx.x / a.Hq, BQ);
   if (qb.b < 0) return;
-  const int b = qb.b;
+  const int b = __builtin_amdgcn_readfirstlane(qb.b);
+  qb.q_begin = __builtin_amdgcn_readfirstlane(qb.q_begin);
+  qb.q_end = __builtin_amdgcn_readfirstlane(qb.q_end);
   const int g = h / (a.Hq / a.Hkv);
-  const int n0 = st.pos0(b);
-  const int qrow0 = st.q_cu[b], krow0 = st.k_beg(b);
-  const int qrow_raw = qb.q_begin + threadIdx.x;
-  const int qrow = min(qrow_raw, qb.q_end - 1);
-  const int qpos = n0 + (qrow_raw - qrow0);
-  const int nk = n0 + (qb.q_end - 1 - qrow0) + 1;
+  const int n0 = __builtin_amdgcn_readfirstlane(st.pos0(b));
+  const int qrow0 = __builtin_amdgcn_readfirstlane(st.q_cu[b]);
+  const int krow0 = __builtin_amdgcn_readfirstlane(st.k_beg(b));
+  const int qrow_raw = qb.q_begin + fr, qrow = min(qrow_raw, qb.q_end - 1);
+  const int qi = qrow - qrow0;                     // this lane's query among its sequence's
+  const int nk1 = qb.q_end - qrow0;                // segment-1 keys this block needs
+  const int P0 = (n0 + KT - 1) / KT;               // no tile mixes the key segments
+  const int ntiles = P0 + (nk1 + KT - 1) / KT;
   const int64_t kv_ld = (int64_t)a.Hkv * D;
-  float q[D], o[D];
-  const float* qp = (const float*)a.q + (int64_t)qrow * a.q_ld + h * D;
+
+  float4 q[NC];
+  const float* qp = (const float*)a.q + (int64_t)qrow * a.q_ld + h * D + 4 * fk;
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
-    q[i] = qp[i];
-    o[i] = 0.f;
-  }
+  for (int j = 0; j < NC; ++j) q[j] = *reinterpret_cast<const float4*>(qp + 8 * j);
+
+  // first key row of tile t and the number of its keys that exist (rows past them re-read
+  // the last one; their scores are masked)
+  auto tile_rows = [&](int t, const float** k, const float** v, int* cnt) {
+    const bool s0 = t < P0;
+    const int first = s0 ? t * KT : (t - P0) * KT;
+    const int64_t off = (int64_t)((s0 ? krow0 : qrow0) + first) * kv_ld + (int64_t)g * D;
+    *k = (const float*)(s0 ? a.k0 : a.k1) + off;
+    *v = (const float*)(s0 ? a.v0 : a.v1) + off;
+    *cnt = min(KT, (s0 ? n0 : nk1) - first);
+  };
+  float4 kf[NC];
+  auto load_k = [&](int t) {
+    const float *k, *v;
+    int cnt;
+    tile_rows(t, &k, &v, &cnt);
+    const float* kp = k + (int64_t)min(fr, cnt - 1) * kv_ld + 4 * fk;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) kf[j] = *reinterpret_cast<const float4*>(kp + 8 * j);
+  };
+  f32x16_t o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
   float m = -INFINITY, l = 0.f;
-  for (int t0 = 0; t0 < nk; t0 += KT) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < KT * D; idx += 64) {
-      const int key = idx / D, c = idx % D;
-      const int kv = min(t0 + key, nk - 1);
-      const int64_t roff = kv < n0 ? (int64_t)(krow0 + kv) * kv_ld : (int64_t)(qrow0 + kv - n0) * kv_ld;
-      Ksh[key][c] = ((const float*)(kv < n0 ? a.k0 : a.k1))[roff + g * D + c];
-      Vsh[key][c] = ((const float*)(kv < n0 ? a.v0 : a.v1))[roff + g * D + c];
+  if (wave < ntiles) load_k(wave);
+  for (int t = wave; t < ntiles; t += NW) {
+    const float *kb, *vb;
+    int cnt;
+    tile_rows(t, &kb, &vb, &cnt);
+    float vf[DB][16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float* vp = vb + (int64_t)min(8 * (e >> 2) + 4 * fk + (e & 3), cnt - 1) * kv_ld + fr;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) vf[db][e] = vp[db * 32];
     }
-    __syncthreads();
-    const int kend = min(KT, nk - t0);
-    for (int j = 0; j < kend; ++j) {
-      if (t0 + j > qpos) break;
-      float sdot = 0.f;
+    f32x16_t s;
 #pragma unroll
-      for (int i = 0; i < D; ++i) sdot = fmaf(q[i], Ksh[j][i], sdot);
-      const float sv = sdot * a.scale;
-      const float mn = fmaxf(m, sv);
-      const float alpha = expf(m - mn), p = expf(sv - mn);
-      l = l * alpha + p;
+    for (int e = 0; e < 16; ++e) s[e] = 0.f;
 #pragma unroll
-      for (int i = 0; i < D; ++i) o[i] = fmaf(p, Vsh[j][i], o[i] * alpha);
-      m = mn;
+    for (int j = 0; j < NC; ++j) {
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].x, q[j].x, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].y, q[j].y, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].z, q[j].z, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].w, q[j].w, s, 0, 0, 0);
+    }
+    if (t + NW < ntiles) load_k(t + NW);
+    // s[e] = score(key 8 (e/4) + 4 fk + e%4 of the tile, query fr); last visible key of the tile:
+    const int lim = (t < P0 ? cnt - 1 : min(cnt - 1, qi - (t - P0) * KT)) - 4 * fk;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      s[e] = 8 * (e >> 2) + (e & 3) <= lim ? s[e] * a.scale : -INFINITY;
+      mx = fmaxf(mx, s[e]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+    const float mn = fmaxf(m, mx);  // every query sees a key of every tile its block visits
+    const float alpha = expf(m - mn);
+    m = mn;
+    l *= alpha;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      s[e] = 8 * (e >> 2) + (e & 3) <= lim ? expf(s[e] - mn) : 0.f;
+      l += s[e];
+    }
+    // A masked key's weight is 0, and 0 * inf would leak a non-finite value of a later token
+    // into an earlier query: the causal tile of such values is added key by key instead.
+    bool odd = false;
+    if (t >= P0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) odd |= !(fabsf(vf[db][e]) <= 3.4028235e38f);
+      odd = __any(odd);
+    }
+    if (!odd) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db][e], s[e], o[db], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        for (int f = 0; f < 2; ++f) {  // key 8 (e/4) + 4 f + e%4: its weight sits in half f
+          const int key = 8 * (e >> 2) + 4 * f + (e & 3);
+          const float pk = __shfl(s[e], fr + 32 * f, kWave);
+          const bool seen = key - 4 * fk <= lim;
+          const float* vp = vb + (int64_t)min(key, cnt - 1) * kv_ld;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+              if (seen) o[db][c] = fmaf(pk, vp[db * 32 + 8 * (c >> 2) + 4 * fk + (c & 3)], o[db][c]);
+        }
     }
   }
-  if (qrow_raw < qb.q_end) {
-    float* op = (float*)a.o + (int64_t)qrow * a.Hq * D + h * D;
-    const float inv = 1.0f / l;
+  // ---- combine the waves: o[db][e] = O^T(dim db*32 + 8 (e/4) + 4 fk + e%4, query fr) ----
+  l += __shfl_xor(l, 32, kWave);
 #pragma unroll
-    for (int i = 0; i < D; ++i) op[i] = o[i] * inv;
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      part[wave][db * 4 + c][lane] = make_float4(o[db][4 * c], o[db][4 * c + 1], o[db][4 * c + 2], o[db][4 * c + 3]);
+  ml[wave][lane] = make_float2(m, l);
+  __syncthreads();
+  float M = -INFINITY, L = 0.f, f[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, ml[w][lane].x);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    f[w] = w < ntiles ? expf(ml[w][lane].x - M) : 0.f;
+    L += ml[w][lane].y * f[w];
+  }
+  const float inv = 1.0f / L;
+  if (qrow_raw >= qb.q_end) return;
+  float* op = (float*)a.o + (int64_t)qrow * a.Hq * D + h * D + 4 * fk;
+  for (int c = wave; c < DB * 4; c += NW) {
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w >= ntiles) continue;
+      const float4 x = part[w][c][lane];
+      v[0] = fmaf(x.x, f[w], v[0]);
+      v[1] = fmaf(x.y, f[w], v[1]);
+      v[2] = fmaf(x.z, f[w], v[2]);
+      v[3] = fmaf(x.w, f[w], v[3]);
+    }
+    *reinterpret_cast<float4*>(op + (c >> 2) * 32 + 8 * (c & 3)) =
+        make_float4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
   }
 }
 
@@ -587,11 +706,11 @@ hipError_t launch_attention(hipStream_t s, rp_dtype dt, const SeqTable& st, cons
     });
     if (e != hipSuccess) return e;
   } else {
-    const int nqb = count_qblocks(st, 64);
-    if (a.D == 128)
-      k_attn_f32<128><<<nqb * a.Hq, 64, 0, s>>>(st, a);
+    const int nqb = count_qblocks(st, 32);
+    if (a.D == 128)  // the fragments of 128 dimensions need the registers of one wave per SIMD
+      k_attn_f32<128, 4><<<nqb * a.Hq, 256, 0, s>>>(st, a);
     else
-      k_attn_f32<64><<<nqb * a.Hq, 64, 0, s>>>(st, a);
+      k_attn_f32<64, 8><<<nqb * a.Hq, 512, 0, s>>>(st, a);
   }
   return hipGetLastError();
 }

@@ -20,7 +20,7 @@
 //     wave's 128 B rows are 64 gate + the matching 64 up rows, so gate and up of one
 //     output feature land in the same lane), and fp32 split-K partials.
 //
-// fp32: a plain 64x64 SIMT tile (exact fp32 FMAs) for the fp32 model.
+// fp32: 32x32 tiles of v_mfma_f32_32x32x2 (exact fp32 products) for the fp32 model.
 #include "gemm_common.h"
 
 #include <stdlib.h>
@@ -669,70 +669,85 @@ void k_gemm_bf16_dma(GemmArgs g) {
 }
 
 // ------------------------------------------------------------------------------------
-// fp32 SIMT GEMM (exact fp32 products, fp32 accumulation)
+// fp32 MFMA GEMM (v_mfma_f32_32x32x2: exact fp32 products, fp32 accumulation).
+// A 32x32 tile per workgroup; its four waves take a quarter of K each and their sums are
+// added in LDS, so that also the few hundred rows of a small fp32 model fill the chip.  Wave
+// fragments come straight from global memory: lane l holds row l % 32 and the four k of half
+// l / 32 of every 8 (the same k for A and B), one 16-byte load for four MFMAs, 32 k (a
+// 128-byte line per row) loaded ahead.  Bound by load latency at these sizes: 1024 x 256 x
+// 688 takes 12 us (launch and timing events included), where 64x64 tiles of VALU products
+// through LDS took 144; 1024 x 1376 x 256 21 us, from 43.
 // ------------------------------------------------------------------------------------
-constexpr int GF_M = 64, GF_N = 64, GF_K = 16;
+constexpr int GF_M = 32, GF_N = 32, GF_K = 16;
 
 template <int EPI, bool BT = false>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
-  __shared__ float As[GF_K][GF_M + 1];
-  __shared__ float Bs[GF_K][GF_N + 1];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  __shared__ float4 red[4][GF_M * GF_N / 4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int tm, tn;
-  tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, &tm, &tn);
-  const int m0 = tm * GF_M, n0 = tn * GF_N;
+  tile_coords(xcd_remap(blockIdx.x, gridDim.x), g.tiles_m, g.tiles_n, &tm, &tn);
   const int kbeg = blockIdx.y * g.k_chunk;
-  const int kend = min(g.K, kbeg + g.k_chunk);
-  float acc[4][4] = {};
-  const float* A = (const float*)g.A;
-  for (int k0 = kbeg; k0 < kend; k0 += GF_K) {
+  const int nch = (min(g.K, kbeg + g.k_chunk) - kbeg) / 8;  // chunks of 8 k (K % 8 == 0)
+  const int per = (nch + 3) / 4, c0 = min(wave * per, nch), c1 = min(c0 + per, nch);
+  const int fr = lane & 31, fk = lane >> 5;
+  const int n = min(tn * GF_N + fr, g.N - 1);
+  const float* Ap = (const float*)g.A + (int64_t)min(tm * GF_M + fr, g.M - 1) * g.lda + kbeg + 4 * fk;
+  const float* Bp = BT ? (const float*)g.B.b0 + (int64_t)(kbeg + 4 * fk) * g.ldb + n
+                       : brow<float>(g.B, n, g.ldb) + kbeg + 4 * fk;
+  auto load = [&](int c, float4 (&a)[4], float4 (&b)[4]) {  // chunks c .. c+3; zeros past the wave's range
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = tid + 256 * i;
-      const int r = idx >> 4, kk = idx & 15;
-      const int m = m0 + r, k = k0 + kk;
-      As[kk][r] = (m < g.M && k < kend) ? A[(int64_t)m * g.lda + k] : 0.f;
-      if (BT) {  // consecutive threads read consecutive columns of a stored [K][N] row
-        const int rn = idx & 63, kn = idx >> 6, n = n0 + rn, k2 = k0 + kn;
-        Bs[kn][rn] = (n < g.N && k2 < kend) ? ((const float*)g.B.b0)[(int64_t)k2 * g.ldb + n] : 0.f;
-      } else {
-        const int n = n0 + r;
-        Bs[kk][r] = (n < g.N && k < kend) ? brow<float>(g.B, n, g.ldb)[k] : 0.f;
+    for (int u = 0; u < 4; ++u) {
+      a[u] = b[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (c + u < c1) {
+        const int k = (c + u) * 8;
+        a[u] = *reinterpret_cast<const float4*>(Ap + k);
+        if (BT) {
+          const float* p = Bp + (int64_t)k * g.ldb;
+          b[u] = make_float4(p[0], p[g.ldb], p[2 * (int64_t)g.ldb], p[3 * (int64_t)g.ldb]);
+        } else {
+          b[u] = *reinterpret_cast<const float4*>(Bp + k);
+        }
       }
     }
-    __syncthreads();
+  };
+  f32x16_t acc;
 #pragma unroll
-    for (int kk = 0; kk < GF_K; ++kk) {
-      float a[4], b[4];
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  auto mma = [&](const float4 (&a)[4], const float4 (&b)[4]) {  // B first: four columns of a row per lane
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    for (int u = 0; u < 4; ++u) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[u].x, a[u].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[u].y, a[u].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[u].z, a[u].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[u].w, a[u].w, acc, 0, 0, 0);
     }
-    __syncthreads();
+  };
+  float4 a0[4], b0[4], a1[4], b1[4];
+  load(c0, a0, b0);
+  for (int c = c0; c < c1; c += 8) {
+    load(c + 4, a1, b1);
+    mma(a0, b0);
+    load(c + 8, a0, b0);
+    mma(a1, b1);
   }
+  // acc[e] = C(row fr, column 8 (e/4) + 4 fk + e%4); 16-byte chunk q of row r at q ^ (r & 7)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty + 16 * i;
-    if (m >= g.M) continue;
+  for (int q = 0; q < 4; ++q)
+    red[wave][fr * 8 + ((2 * q + fk) ^ (fr & 7))] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+  __syncthreads();
+  const int r = tid >> 3, q = tid & 7, m = tm * GF_M + r;
+  if (m >= g.M) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx + 16 * j;
-      if (n >= g.N) continue;
-      const float v = acc[i][j];
-      if (EPI == -1) {
-        g.partials[((int64_t)blockIdx.y * g.M + m) * g.N + n] = v;
-      } else if (EPI == EPI_ADD_F32) {
-        ((float*)g.C)[(int64_t)m * g.ldc + n] += v;
-      } else {
-        ((float*)g.C)[(int64_t)m * g.ldc + n] = v;
-      }
-    }
+  for (int w = 0; w < 4; ++w) {
+    const float4 x = red[w][r * 8 + (q ^ (r & 7))];
+    v[0] += x.x;
+    v[1] += x.y;
+    v[2] += x.z;
+    v[3] += x.w;
   }
+  const F32Out out = f32_out<EPI>(g);
+  store4<EPI == EPI_ADD_F32>(out.p + (int64_t)m * out.ld, tn * GF_N + 4 * q, g.N, v, out.vec);
 }
 
 // ------------------------------------------------------------------------------------
