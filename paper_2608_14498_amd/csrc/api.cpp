@@ -424,8 +424,8 @@ struct DecodeWS {
   rp::ArgmaxPart* arg_part;  // per-wave row candidates of the fused lm_head + argmax
 };
 
-// When the caller wants no logits, the lm_head of a 16-bit model with at most 64 rows
-// reduces each row to its argmax in the GEMM (the [B, V] logits are never stored).
+// The lm_head of a 16-bit model with at most 64 rows reduces each row to its argmax in the
+// GEMM (the [B, V] logits are stored only if the caller wants them).
 bool decode_fused_argmax(const rp_model* m, int32_t B) {
   const rp_config& c = m->cfg;
   return rp::gemm_argmax_supported(c.dtype, B, c.vocab, c.d_model, c.d_model, c.d_model);
@@ -1106,7 +1106,7 @@ rp_status decode_run(const rp_model* m, void* stream, int32_t B, rp_kv cache, in
                                                                        Hkv, D, lw.bq, lw.bk, lw.bv, m->rope, kv_len,
                                                                        cap, c.max_position, w.L.Q, kl, vl));
     RP_TRY_LAUNCH_N("decode.attention", rp::launch_decode_attention(s, dt, w.L.Q, hq, kl, vl, kv_len, cap, c.max_position, B, Hq, Hkv,
-                                              D, scale, w.attn_part, w.L.O));
+                                              D, scale, w.attn_part, w.L.QKV, (int64_t)B * qkv, w.L.O));
     const rp::BSeg bo = wo_operand(c, lw);
     const int s_o = decode_splitk(c, B, d, hq);
     RP_TRY_LAUNCH_N("decode.gemm_o_proj", rp::launch_gemm(s, dt, B, d, hq, w.L.O, hq, bo, bo.trans ? d : hq, nullptr,
@@ -1116,10 +1116,18 @@ rp_status decode_run(const rp_model* m, void* stream, int32_t B, rp_kv cache, in
                                                                         w.L.X, lw.mlp_norm, c.rms_eps, w.L.N));
     rp::BSeg bgu = {lw.w_gate, lw.w_up, lw.w_up, F, 2 * F};
     const int s_gu = decode_splitk(c, B, 2 * F, d);
-    RP_TRY_LAUNCH_N("decode.gemm_gate_up", rp::launch_gemm(s, dt, B, 2 * F, d, w.L.N, d, bgu, d, nullptr, 2 * F,
-                                                           rp::EPI_PARTIALS, s_gu, w.gemm_part));
-    RP_TRY_LAUNCH_N("decode.swiglu", rp::launch_splitk_swiglu(s, dt, w.gemm_part, rp::gemm_effective_splitk(dt, d, s_gu),
-                                                              B, F, w.L.ACT));
+    // K whole and SwiGLU in the epilogue where the 80-feature tiles alone fill most of the
+    // chip (160 of them); the chunks are added as the partials were: the same bits.  7B: 64
+    // rows 51 us, from 60 + 3 (two splits and the summing SwiGLU kernel).
+    if (F >= 160 * 80 && rp::gemm_swiglu_chunks(dt, B, F, d, s_gu)) {
+      RP_TRY_LAUNCH_N("decode.gemm_gate_up", rp::launch_gemm(s, dt, B, F, d, w.L.N, d, bgu, d, w.L.ACT, F,
+                                                             rp::EPI_SWIGLU, s_gu, nullptr));
+    } else {
+      RP_TRY_LAUNCH_N("decode.gemm_gate_up", rp::launch_gemm(s, dt, B, 2 * F, d, w.L.N, d, bgu, d, nullptr, 2 * F,
+                                                             rp::EPI_PARTIALS, s_gu, w.gemm_part));
+      RP_TRY_LAUNCH_N("decode.swiglu", rp::launch_splitk_swiglu(s, dt, w.gemm_part,
+                                                                rp::gemm_effective_splitk(dt, d, s_gu), B, F, w.L.ACT));
+    }
     const rp::BSeg bd = w_down_operand(c, lw);
     const int s_down = decode_splitk(c, B, d, F);
     RP_TRY_LAUNCH_N("decode.gemm_down", rp::launch_gemm(s, dt, B, d, F, w.L.ACT, F, bd, bd.trans ? d : F, nullptr, d,
@@ -1129,8 +1137,8 @@ rp_status decode_run(const rp_model* m, void* stream, int32_t B, rp_kv cache, in
                                                                         w.L.X, next_norm, c.rms_eps, w.L.N));
   }
   rp::BSeg blm = {m->lm_head, m->lm_head, m->lm_head, c.vocab, c.vocab};
-  if (!logits && w.arg_part) {
-    RP_TRY_LAUNCH_N("decode.gemm_lm_head_argmax", rp::launch_gemm_argmax(s, dt, B, c.vocab, d, w.L.N, d, blm, d,
+  if (w.arg_part) {
+    RP_TRY_LAUNCH_N("decode.gemm_lm_head_argmax", rp::launch_gemm_argmax(s, dt, B, c.vocab, d, w.L.N, d, blm, d, logits,
                                                                          w.arg_part, next_ids));
     return dbg.end(RP_OK);
   }

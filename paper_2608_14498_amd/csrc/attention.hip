@@ -22,6 +22,8 @@
 #include "device_common.h"
 #include "rp_internal.h"
 
+#include <type_traits>
+
 namespace rp {
 
 struct QBlock {
@@ -898,12 +900,20 @@ __global__ __launch_bounds__(256) void k_decode_attn_part(const T* __restrict__ 
 // DC_WAVES-th of one record per chunk.
 constexpr int DC_WAVES = 3;
 __host__ __device__ inline int decode_groups(int nchunks) { return (nchunks + DC_WAVES - 1) / DC_WAVES; }
-template <typename T16, int D>
-__global__ __launch_bounds__(64 * DC_WAVES) void k_decode_attn_mfma(const T16* __restrict__ q, int q_ld,
+// DEEP: a launch whose chunks are no more than the compute units runs one wave per chunk
+// with a 5-stage ring instead (four tiles ahead: a lone wave with two is bound by the latency
+// of HBM, 1.1 us a tile).  The chunks' records then go to `part` and `sums`, and
+// k_decode_chunk_merge combines them as the workgroups and the merge do here, operation for
+// operation: the same bits.  One sequence of 4000 keys, 4 kv heads of 128: 42 -> 32 us a layer
+// (launches and timing events included).
+constexpr int DC_DEEP = 5;  // four tiles ahead: 64 copies, about what a wave can have outstanding
+template <typename T16, int D, bool DEEP>
+__global__ __launch_bounds__(64 * (DEEP ? 1 : DC_WAVES)) void k_decode_attn_mfma(const T16* __restrict__ q, int q_ld,
                                                                     const T16* __restrict__ ck, const T16* __restrict__ cv,
                                                                     const int32_t* __restrict__ kv_len, int cap,
                                                                     int max_pos, int B, int Hq, int Hkv, float scale,
-                                                                    int nchunks, float* __restrict__ part) {
+                                                                    int nchunks, float* __restrict__ part,
+                                                                    float4* __restrict__ sums, T16* __restrict__ out) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef Half16<T16> H;
   typedef typename H::V8 V8;
@@ -916,18 +926,21 @@ __global__ __launch_bounds__(64 * DC_WAVES) void k_decode_attn_mfma(const T16* _
   static_assert(NT % 3 == 0 || NT > 3, "ring");
   constexpr int PSL = KT * CH * 4 / 64;  // floats per lane in one K stage
   static_assert(DB * 16 <= 2 * PSL && PSL >= 2, "merge data fits the wave's K stages");
-  __shared__ u32x4_t Ksa[DC_WAVES][KT * CH], Ksb[DC_WAVES][KT * CH], Ksc[DC_WAVES][KT * CH];
-  __shared__ u32x4_t Vsa[DC_WAVES][KT * CH], Vsb[DC_WAVES][KT * CH], Vsc[DC_WAVES][KT * CH];
+  constexpr int NW = DEEP ? 1 : DC_WAVES;
+  constexpr int SH = DEEP ? 1 : KT * CH, SD = DEEP ? 2 * KT * CH : 1;
+  __shared__ u32x4_t Ksa[NW][SH], Ksb[NW][SH], Ksc[NW][SH];
+  __shared__ u32x4_t Vsa[NW][SH], Vsb[NW][SH], Vsc[NW][SH];
+  __shared__ u32x4_t R0[SD], R1[SD], R2[SD], R3[SD], R4[SD];  // K tile, then V tile
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   u32x4_t *Ks0 = Ksa[wave], *Ks1 = Ksb[wave], *Ks2 = Ksc[wave];
   u32x4_t *Vs0 = Vsa[wave], *Vs1 = Vsb[wave], *Vs2 = Vsc[wave];
   // kv head fastest: the Hkv workgroups that read the same cache rows (each its own
   // 2*D-byte slice of a row) are dispatched together, so each row is fetched while open
-  const int nrec = decode_groups(nchunks);
+  const int nrec = DEEP ? nchunks : decode_groups(nchunks);
   const int g = blockIdx.x % Hkv, bgr = blockIdx.x / Hkv;
   const int grp = bgr % nrec, b = bgr / nrec;
-  const int c = grp * DC_WAVES + wave;
+  const int c = grp * NW + wave;
   const int G = Hq / Hkv;
   // query columns: lane column fr is q head g*G + fr (zero beyond G); issued first, so they
   // are in flight while kv_len is read and are covered by the wait for the first tile
@@ -1041,6 +1054,30 @@ __global__ __launch_bounds__(64 * DC_WAVES) void k_decode_attn_mfma(const T16* _
   // ahead of the copies, so no register load is pending when the loop starts (a loop
   // whose loads fill only LDS but which reads registers still loading from before it
   // makes the compiler drain every load, these copies included, ahead of the loop).
+  if constexpr (DEEP) {
+    // every copy is issued, also past the chunk's tiles (out of range: nothing is fetched), so
+    // the compiler counts them exactly; tile 0 runs before the loop as below
+#define DD_LOAD(R_, t_) DM_LOAD(R_, (R_) + KT * CH, t_)
+#define DD_STEP(R_, u_)                                  \
+  if (t + (u_) < ntiles) tile(R_, R_ + KT * CH, t + (u_)); \
+  DD_LOAD(R_, t + (u_) + DC_DEEP);
+    DD_LOAD(R0, 0);
+    DD_LOAD(R1, 1);
+    DD_LOAD(R2, 2);
+    DD_LOAD(R3, 3);
+    DD_LOAD(R4, 4);
+    tile(R0, R0 + KT * CH, 0);
+    DD_LOAD(R0, DC_DEEP);
+    for (int t = 1; t < ntiles; t += DC_DEEP) {
+      DD_STEP(R1, 0);
+      DD_STEP(R2, 1);
+      DD_STEP(R3, 2);
+      DD_STEP(R4, 3);
+      DD_STEP(R0, 4);
+    }
+#undef DD_LOAD
+#undef DD_STEP
+  } else {
   DM_LOAD(Ks0, Vs0, 0);
   DM_LOAD(Ks1, Vs1, min(1, ntiles - 1));
   DM_LOAD(Ks2, Vs2, min(2, ntiles - 1));
@@ -1063,8 +1100,25 @@ __global__ __launch_bounds__(64 * DC_WAVES) void k_decode_attn_mfma(const T16* _
   if (r > 2) tile(Ks0, Vs0, t + 2);
   if (r > 3) tile(Ks1, Vs1, t + 3);
   if (r > 4) tile(Ks2, Vs2, t + 4);
+  }
 #undef DM_LOAD
   __builtin_amdgcn_s_waitcnt(0);  // this wave's copies have landed: its stages are free
+  }
+  if constexpr (DEEP) {  // this chunk's record
+    const float lo = __shfl_xor(l_run, 32, kWave);
+    if (fr < G) {
+      const int64_t rec = (int64_t)(b * Hq + g * G + fr) * nchunks + c;
+      if (fk == 0) sums[rec] = make_float4(m_run, l_run, lo, 0.f);  // (kMaskVal, 0, 0) without keys
+      if (nkeys > 0) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4)
+            *reinterpret_cast<float4*>(part + rec * D + db * 32 + 8 * e4 + 4 * fk) =
+                make_float4(o[db][4 * e4], o[db][4 * e4 + 1], o[db][4 * e4 + 2], o[db][4 * e4 + 3]);
+      }
+    }
+    return;
   }
   // ---- combine the group's chunks: waves 1.. leave o in their own first two K stages and
   // (max, sum) in the third (lane-major, conflict-free); wave 0 rescales them to the
@@ -1120,6 +1174,21 @@ __global__ __launch_bounds__(64 * DC_WAVES) void k_decode_attn_mfma(const T16* _
       }
   }
   const float l = lsum + __shfl_xor(lsum, 32, kWave);
+  if (nrec == 1) {  // the sequence's only record: the result itself, as the merge would form it
+    if (fr < G) {
+      const float inv = 1.0f / l;
+      T16* oh = out + (int64_t)(b * Hq + g * G + fr) * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+          const float v[4] = {o[db][4 * e4] * inv, o[db][4 * e4 + 1] * inv, o[db][4 * e4 + 2] * inv,
+                              o[db][4 * e4 + 3] * inv};
+          store4(oh + db * 32 + 8 * e4 + 4 * fk, v);
+        }
+    }
+    return;
+  }
   if (fr < G) {
     const int64_t rec = (int64_t)(b * Hq + g * G + fr) * nrec + grp;
     float* oh = part + rec * D;
@@ -1136,6 +1205,69 @@ __global__ __launch_bounds__(64 * DC_WAVES) void k_decode_attn_mfma(const T16* _
       }
   }
 #endif
+}
+
+// Merge of the DEEP kernel's chunk records, one wave per (sequence, q head): lane r combines
+// the sums of chunks 3 r .. 3 r + 2 as wave 0 of a workgroup does above (each half wave's sum
+// apart, then added), the groups are merged as in k_decode_attn_merge, and each lane forms its
+// D/64 dimensions of every group's o on the way.  At most 64 groups.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_decode_chunk_merge(const float* __restrict__ part,
+                                                            const float4* __restrict__ sums, int nchunks, int items,
+                                                            T* __restrict__ o) {
+  constexpr int PER = D / 64;
+  static_assert(DC_WAVES == 3, "groups of three chunks");
+  const int item = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (item >= items) return;
+  const int nrec = decode_groups(nchunks);
+  const float4 none = make_float4(kMaskVal, 0.f, 0.f, 0.f);
+  float4 s[3];
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    const int c = lane * 3 + w;
+    s[w] = c < nchunks ? sums[(int64_t)item * nchunks + c] : none;
+  }
+  float M3 = s[0].x;
+#pragma unroll
+  for (int w = 1; w < 3; ++w) M3 = fmaxf(M3, s[w].x);
+  float f[3];
+#pragma unroll
+  for (int w = 0; w < 3; ++w) f[w] = __builtin_amdgcn_exp2f(s[w].x - M3);
+  float l0 = s[0].y * f[0], l1 = s[0].z * f[0];
+#pragma unroll
+  for (int w = 1; w < 3; ++w) {
+    l0 = fmaf(s[w].y, f[w], l0);
+    l1 = fmaf(s[w].z, f[w], l1);
+  }
+  const bool has = lane < nrec && s[0].x > kMaskVal;  // chunks with keys come first
+  const float mc = has ? M3 * 0.6931471805599453f : -INFINITY;
+  const float M = wave_max(mc);
+  const float wt = has ? expf(mc - M) : 0.f;
+  const float L = wave_sum(has ? wt * (l0 + l1) : 0.f);
+  const int nv = __popcll(__ballot(has));
+  float acc[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+  for (int r = 0; r < nv; ++r) {
+    const float wr = __shfl(wt, r, kWave);
+    const float* oc = part + ((int64_t)item * nchunks + 3 * r) * D + lane * PER;
+    float og[PER];
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+      const float fw = __shfl(f[w], r, kWave);
+      const bool in = __shfl(s[w].x, r, kWave) > kMaskVal;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const float x = in ? oc[w * D + e] : 0.f;
+        og[e] = w == 0 ? x * fw : fmaf(x, fw, og[e]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] = fmaf(wr, og[e], acc[e]);
+  }
+  const float inv = 1.0f / L;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) stf(o + (int64_t)item * D + lane * PER + e, acc[e] * inv);
 }
 
 // Merge of the decode chunks: one wave per (sequence, q head).  Lane c holds chunk c's
@@ -1185,7 +1317,7 @@ size_t decode_attn_partial_floats(int32_t B, int32_t Hq, int32_t D, int32_t cap)
 hipError_t launch_decode_attention(hipStream_t s, rp_dtype dt, const void* q, int32_t q_ld,
                                    const void* cache_k, const void* cache_v, const int32_t* kv_len,
                                    int32_t cap, int32_t max_pos, int32_t B, int32_t Hq, int32_t Hkv,
-                                   int32_t D, float scale, float* partials, void* o) {
+                                   int32_t D, float scale, float* partials, float* sums, int64_t sums_floats, void* o) {
   const int nchunks = (cap + DC_KEYS - 1) / DC_KEYS;
   if (dt == RP_F32) {
     const int grid = (B * Hkv * nchunks + 3) / 4;  // one wave per chunk, 4 waves per workgroup
@@ -1208,20 +1340,30 @@ hipError_t launch_decode_attention(hipStream_t s, rp_dtype dt, const void* q, in
   // the 16-bit kernel addresses a sequence's cache rows with 32-bit byte offsets
   if ((int64_t)cap * Hkv * D * 2 > (int64_t)INT32_MAX) return hipErrorInvalidValue;
   const int nrec = decode_groups(nchunks);
-  const int grid = B * Hkv * nrec;  // one workgroup per group of DC_WAVES chunks
+  // One wave per chunk where each can have a compute unit to itself (and the records fit).
+  const bool deep = (int64_t)B * Hkv * nchunks <= 256 && nrec <= 64 && sums && !((uintptr_t)sums & 15) &&
+                    (int64_t)B * Hq * nchunks * 4 <= sums_floats;
+  const int grid = B * Hkv * (deep ? nchunks : nrec), mgrid = (B * Hq + 3) / 4;
   with_half16(dt, [&](auto tag_) {
     using H = decltype(tag_);
-    if (D == 128) {
-      k_decode_attn_mfma<H, 128><<<grid, 64 * DC_WAVES, 0, s>>>((const H*)q, q_ld, (const H*)cache_k,
-                                                               (const H*)cache_v, kv_len, cap, max_pos, B, Hq, Hkv,
-                                                               scale, nchunks, partials);
-      k_decode_attn_merge<H, 128><<<(B * Hq + 3) / 4, 256, 0, s>>>(partials, nrec, B * Hq, (H*)o);
-    } else {
-      k_decode_attn_mfma<H, 64><<<grid, 64 * DC_WAVES, 0, s>>>((const H*)q, q_ld, (const H*)cache_k,
-                                                              (const H*)cache_v, kv_len, cap, max_pos, B, Hq, Hkv,
-                                                              scale, nchunks, partials);
-      k_decode_attn_merge<H, 64><<<(B * Hq + 3) / 4, 256, 0, s>>>(partials, nrec, B * Hq, (H*)o);
-    }
+    auto run = [&](auto d_) {
+      constexpr int DD = decltype(d_)::value;
+      if (deep) {
+        k_decode_attn_mfma<H, DD, true><<<grid, 64, 0, s>>>((const H*)q, q_ld, (const H*)cache_k, (const H*)cache_v,
+                                                            kv_len, cap, max_pos, B, Hq, Hkv, scale, nchunks, partials,
+                                                            (float4*)sums, (H*)o);
+        k_decode_chunk_merge<H, DD><<<mgrid, 256, 0, s>>>(partials, (const float4*)sums, nchunks, B * Hq, (H*)o);
+        return;
+      }
+      k_decode_attn_mfma<H, DD, false><<<grid, 64 * DC_WAVES, 0, s>>>((const H*)q, q_ld, (const H*)cache_k,
+                                                                      (const H*)cache_v, kv_len, cap, max_pos, B, Hq,
+                                                                      Hkv, scale, nchunks, partials, nullptr, (H*)o);
+      if (nrec > 1) k_decode_attn_merge<H, DD><<<mgrid, 256, 0, s>>>(partials, nrec, B * Hq, (H*)o);
+    };
+    if (D == 128)
+      run(std::integral_constant<int, 128>());
+    else
+      run(std::integral_constant<int, 64>());
   });
   return hipGetLastError();
 }

@@ -853,7 +853,7 @@ struct SkinnyArgs {
   int64_t plane;  // elements between splits of out
   int k_chunk;
   int add;        // accumulate into out (one split)
-  ArgmaxPart* arg;  // instead of out (one split): each wave's per-row (max, lowest column of it), [M][ceil(N/32)]
+  ArgmaxPart* arg;  // one split, out may be NULL: each wave's per-row (max, lowest column of it), [M][ceil(N/32)]
 };
 
 template <typename T16, int RF, bool BT, int SW>
@@ -997,7 +997,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_skinny(SkinnyArgs g) {
       if (fk == 0 && m < g.M && nw0 < g.N)
         g.arg[(int64_t)m * ((g.N + 31) / 32) + blockIdx.x * SW + wave] = ArgmaxPart{best, bi};
     }
-    return;
+    if (!g.out) return;
   }
   float* outp = g.out + (int64_t)blockIdx.y * g.plane;
   const bool vec = (g.ldo & 3) == 0 && ((uintptr_t)g.out & 15) == 0 && (g.plane & 3) == 0;
@@ -1098,6 +1098,13 @@ int32_t gemm_effective_splitk(rp_dtype dt, int32_t K, int32_t splitk) {
   return (K + k_chunk - 1) / k_chunk;
 }
 
+// The fused SwiGLU with K summed as split-K partials would be: at most 64 rows, two or three
+// chunks (what k_gemm_flex has the registers for).
+bool gemm_swiglu_chunks(rp_dtype dt, int32_t M, int32_t N, int32_t K, int32_t splitk) {
+  return dt != RP_F32 && M <= 64 && K % GB_K == 0 && gemm_effective_splitk(dt, K, splitk) <= 3 &&
+         (uint64_t)N * K * 2u <= 0xFFFFFF00ull;
+}
+
 hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t K, const void* A,
                        int32_t lda, const BSeg& B, int32_t ldb, void* C, int32_t ldc, Epi epi,
                        int32_t splitk, float* partials, const LseOut* lse, const RopeOut* rope) {
@@ -1108,7 +1115,7 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
        N != rope->hq + 2 * rope->hkv || (rope->hq % rope->D) || (rope->hkv % rope->D) || ((uintptr_t)rope->cs & 15) ||
        (((uintptr_t)rope->q | (uintptr_t)rope->k | (uintptr_t)rope->v) & 7)))
     return hipErrorInvalidValue;
-  if (epi == EPI_SWIGLU && (!half || splitk > 1)) return hipErrorInvalidValue;
+  if (epi == EPI_SWIGLU && (!half || (splitk > 1 && !gemm_swiglu_chunks(dt, M, N, K, splitk)))) return hipErrorInvalidValue;
   if (epi == EPI_LSE && (!half || splitk > 1 || !lse)) return hipErrorInvalidValue;
   if (epi == EPI_PARTIALS && !partials) return hipErrorInvalidValue;
   // a transposed B serves the row-parallel projections: residual or split-K epilogue
@@ -1135,6 +1142,11 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
   if (splitk > kblocks) splitk = kblocks;
   g.k_chunk = ((kblocks + splitk - 1) / splitk) * bk;
   splitk = (K + g.k_chunk - 1) / g.k_chunk;
+  if (epi == EPI_SWIGLU && splitk > 1) {  // the chunks are summed in the kernel
+    g.k_sum = g.k_chunk;
+    g.k_chunk = K;
+    splitk = 1;
+  }
   // EPI_PARTIALS: the partials epilogue even for one split, and no reduction here
   const bool split = splitk > 1 || epi == EPI_PARTIALS;
   const int64_t b_rows = epi == EPI_SWIGLU ? (int64_t)B.n1 + N : N;
@@ -1143,6 +1155,7 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
   // tile's deeper ring then wins (same bits).
   const bool flex = half && dma_setup(g, b_rows, epi == EPI_SWIGLU) &&
                     flex_gemm_wanted(g, split ? -1 : (int)epi, splitk);
+  if (g.k_sum && !flex) return hipErrorInvalidValue;
   if (half && skinny_setup(g, epi, split) && !(flex && !split && N <= 128 * 128)) {
     // split: partials (summed by the caller, or by the reduction below); else C itself
     with_half16(dt, [&](auto tag_) {
@@ -1211,8 +1224,9 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
 }
 
 // C = A . B^T reduced to each row's argmax (the lowest column of the row's maximum; NaN
-// never wins; -1 for a row with no candidate), without storing C: the skinny kernel
-// writes each wave's per-row candidate and k_argmax_parts picks among them in column order.
+// never wins; -1 for a row with no candidate), C stored only if the caller wants it: the
+// skinny kernel writes each wave's per-row candidate and k_argmax_parts picks among them in
+// column order (64 x 152064: 4 us, where reading the stored logits back took 16).
 bool gemm_argmax_supported(rp_dtype dt, int32_t M, int32_t N, int32_t K, int32_t lda, int32_t ldb) {
   if (dt == RP_F32 || M < 1 || N < 1 || M > 64 || K % 64) return false;
   if (gemm_skinny_splitk(M, N, K) != 1 || gemm_effective_splitk(dt, K, gemm_skinny_splitk(M, N, K)) != 1) return false;
@@ -1280,7 +1294,7 @@ __global__ __launch_bounds__(256) void k_argmax_parts(const ArgmaxPart* __restri
 }
 
 hipError_t launch_gemm_argmax(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t K, const void* A,
-                              int32_t lda, const BSeg& B, int32_t ldb, ArgmaxPart* parts, int32_t* out) {
+                              int32_t lda, const BSeg& B, int32_t ldb, float* C, ArgmaxPart* parts, int32_t* out) {
   if (!gemm_argmax_supported(dt, M, N, K, lda, ldb) || B.trans || ((uintptr_t)A & 15) || ((uintptr_t)B.b0 & 15) ||
       !parts || !out)
     return hipErrorInvalidValue;
@@ -1295,7 +1309,7 @@ hipError_t launch_gemm_argmax(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, 
   g.k_chunk = K;
   with_half16(dt, [&](auto tag_) {
     using H = decltype(tag_);
-    launch_skinny<H>(s, g, 1, nullptr, 0, 0, false, parts);
+    launch_skinny<H>(s, g, 1, C, N, 0, false, parts);
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -22,6 +22,7 @@ struct GemmArgs {
   LseOut lse;        // EPI_LSE outputs
   int n_part;        // EPI_LSE column blocks per row
   RopeOut rope;      // EPI_ROPE outputs
+  int k_sum = 0;     // EPI_SWIGLU, at most 64 rows: K summed in chunks of k_sum (0: one chain)
 };
 
 template <typename T>

@@ -23,7 +23,11 @@ __device__ __forceinline__ void wait_vm_barrier() {
 // of the other 16-bit kernels, so every output is the same MFMA chain: the same bits
 // whichever tile computes it.  Bound by the copies (see flex_pick): with the MFMAs and the
 // fragment reads taken out the kernel takes 98-100% of its time, without the copies half.
-template <int EPI, typename T16, int RF, int SW, int NS, bool BT = false>
+// CK (SwiGLU only): K is summed in two or three chunks of k_sum, added in order as
+// launch_splitk_swiglu adds that many split-K partials, so a decode step's gate/up projection
+// keeps the bits of its split form without writing the partials.  (Four chunks, added as
+// (0 + 1) + (2 + 3), need a third set of accumulators: at 160 rows 179 us, 121 split.)
+template <int EPI, typename T16, int RF, int SW, int NS, bool BT = false, bool CK = false>
 __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef __attribute__((address_space(3))) void lds_void;
@@ -47,6 +51,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
   const int m0 = tm * MT;
   const int kbeg = blockIdx.y * g.k_chunk;
   const int KT = (min(g.K, kbeg + g.k_chunk) - kbeg) / GB_K;
+  static_assert(!CK || EPI == EPI_SWIGLU, "chunked sums");
 
   const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, (int)0xFFFFFF00u, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsB0 = __builtin_amdgcn_make_buffer_rsrc((void*)g.B.b0, 0, (int)0xFFFFFF00u, 0x00020000);
@@ -140,6 +145,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
     X_LOAD(S_, (t_) + NS);                             \
     X_REGION(L);                                       \
     __builtin_amdgcn_sched_barrier(0);                 \
+    if (CK && (t_) + 1 == fold_at && fold_at < KT) fold(); \
   }
 
   f32x16_t acc[RF];
@@ -147,6 +153,22 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
   for (int i = 0; i < RF; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+  f32x16_t done[CK ? RF : 1];  // the sum of the chunks that are done
+  bool first = true;
+  int fold_at = CK ? g.k_sum / GB_K : 0;  // slab count at the running chunk's end
+  auto fold = [&]() __attribute__((always_inline)) {
+    if constexpr (CK) {
+#pragma unroll
+      for (int i = 0; i < RF; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          done[i][e] = first ? acc[i][e] : done[i][e] + acc[i][e];
+          acc[i][e] = 0.f;
+        }
+      first = false;
+      fold_at += g.k_sum / GB_K;
+    }
+  };
   const int fr = lane & 31, fk = lane >> 5;
   int afr[4], bfr[4];  // chunk of fragment 0 at each k-step (32 rows on, the swizzle repeats)
 #pragma unroll
@@ -201,6 +223,12 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
 #undef X_MMA
 #undef X_REGION
 #undef X_SLAB
+  if constexpr (CK) {  // the last chunk is still in acc
+#pragma unroll
+    for (int i = 0; i < RF; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][e] = done[i][e] + acc[i][e];
+  }
   wait_vm_barrier<0>();  // no copy into LDS is in flight, every wave has read its fragments
 
   // ---- epilogue through LDS: fp32 rows staged in the idle stages (blocks of 32 rows of NT
@@ -337,11 +365,12 @@ static int flex_cols(const GemmArgs& g, int epi, int SW) {
 static int flex_pick(const GemmArgs& g, int epi, int splitk) {
   const double kt = g.k_chunk / GB_K;
   const int64_t big = (int64_t)((g.M + 255) / 256) * (epi == EPI_SWIGLU ? (g.N + 127) / 128 : (g.N + 255) / 256) * splitk;
-  double best = (double)((big + 255) / 256) * (kt * 1190. + 15000.);
+  double best = g.k_sum ? 1e30 : (double)((big + 255) / 256) * (kt * 1190. + 15000.);
   int pick = -1;
   for (int i = 0; i < (int)(sizeof kFlexTiles / sizeof kFlexTiles[0]); ++i) {
     const FlexTile& f = kFlexTiles[i];
     if (f.SW != 4 && epi != EPI_SWIGLU) continue;
+    if (g.k_sum && f.RF > 2) continue;
     const int64_t tiles = (int64_t)((g.M + 32 * f.RF - 1) / (32 * f.RF)) * flex_cols(g, epi, f.SW) * splitk;
     double slab = 66. * (f.RF + f.SW);
     if (f.SW == 5) slab = std::max(slab, 170. * f.RF);  // five waves on four SIMDs: the MFMAs of two
@@ -366,6 +395,11 @@ static void launch_flex_t(hipStream_t s, int epi, GemmArgs g, int splitk) {
   g.tiles_m = (g.M + 32 * RF - 1) / (32 * RF);
   g.tiles_n = flex_cols(g, epi, SW);
   const dim3 grid(g.tiles_m * g.tiles_n, splitk);
+  if constexpr (RF == 2)
+    if (g.k_sum) {
+      k_gemm_flex<EPI_SWIGLU, T16, RF, SW, NS, false, true><<<grid, SW * 64, 0, s>>>(g);
+      return;
+    }
   if constexpr (SW != 4) {
     k_gemm_flex<EPI_SWIGLU, T16, RF, SW, NS><<<grid, SW * 64, 0, s>>>(g);
   } else {

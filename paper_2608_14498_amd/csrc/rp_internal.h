@@ -151,13 +151,16 @@ hipError_t launch_argmax(hipStream_t s, const float* logits, int32_t B, int32_t 
 
 // GEMM: C[M,N] (epi)= A[M,K] . B[N,K]^T, fp32 accumulation.  For EPI_SWIGLU, N is the
 // number of output features f and B = {b0 = gate [N,K], b1 = up [N,K]} (n1 = N); the fused
-// epilogue writes silu(A.gate_f) * (A.up_f).  splitk > 1 needs EPI != EPI_SWIGLU.
+// epilogue writes silu(A.gate_f) * (A.up_f); splitk > 1 there (where gemm_swiglu_chunks says
+// so) keeps K in one kernel and gives the bits of splitk partials summed by
+// launch_splitk_swiglu.
 hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t K, const void* A,
                        int32_t lda, const BSeg& B, int32_t ldb, void* C, int32_t ldc, Epi epi,
                        int32_t splitk, float* partials, const LseOut* lse = nullptr,
                        const RopeOut* rope = nullptr);
+bool gemm_swiglu_chunks(rp_dtype dt, int32_t M, int32_t N, int32_t K, int32_t splitk);
 // out[m] = argmax over n of (A . B^T)[m][n] (lowest n among equal maxima; NaN never wins; -1
-// when a row has no candidate), C itself never stored.  16-bit, one B segment [N][K], M <= 64,
+// when a row has no candidate); C (fp32 [M][N]) is stored unless NULL.  16-bit, one B segment [N][K], M <= 64,
 // one K split (gemm_argmax_supported).  parts: gemm_argmax_parts(M, N) ArgmaxPart entries.
 struct ArgmaxPart {
   float v;
@@ -166,7 +169,7 @@ struct ArgmaxPart {
 bool gemm_argmax_supported(rp_dtype dt, int32_t M, int32_t N, int32_t K, int32_t lda, int32_t ldb);
 size_t gemm_argmax_parts(int32_t M, int32_t N);
 hipError_t launch_gemm_argmax(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t K, const void* A,
-                              int32_t lda, const BSeg& B, int32_t ldb, ArgmaxPart* parts, int32_t* out);
+                              int32_t lda, const BSeg& B, int32_t ldb, float* C, ArgmaxPart* parts, int32_t* out);
 
 // Rotation table of EPI_ROPE for M rows (float2 [M][D/2]); positions as launch_rope_kv.
 hipError_t launch_rope_table(hipStream_t s, const SeqTable& st, const RopeFreq& rf, int32_t max_pos, const MRope& mr,
@@ -271,9 +274,11 @@ hipError_t launch_rope_kv_splitk(hipStream_t s, rp_dtype dt, const SeqTable& st,
 // X[b] = E[ids[b]] (clamped); out[b] = RMSNorm(X[b]) * w.
 hipError_t launch_decode_embed_norm(hipStream_t s, rp_dtype dt, const int32_t* ids, const void* embed, int32_t vocab,
                                     int32_t B, int32_t d, float* X, const void* w, float eps, void* out);
+// partials: decode_attn_partial_floats; sums: further scratch (sums_floats floats, 16-byte
+// aligned, may be none) that lets few sequences run one wave per chunk.
 hipError_t launch_decode_attention(hipStream_t s, rp_dtype dt, const void* q, int32_t q_ld,
                                    const void* cache_k, const void* cache_v, const int32_t* kv_len,
                                    int32_t cap, int32_t max_pos, int32_t B, int32_t Hq, int32_t Hkv,
-                                   int32_t D, float scale, float* partials, void* o);
+                                   int32_t D, float scale, float* partials, float* sums, int64_t sums_floats, void* o);
 
 }  // namespace rp

@@ -1,0 +1,56 @@
+"""The forms a decode step takes by batch size give one sequence the same bits: alone it runs
+one wave per 1024-key chunk (deep ring, chunk merge), in a large batch three chunks per
+workgroup, with one record (the result written directly) or several.  The gate/up projection
+with its chunked sums (F >= 12800) is compared with the oracle."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2608_14498_amd import configs, inputs
+from paper_2608_14498_amd.runtime import DeviceModel, to_device
+from tests.gpu_helpers import max_abs
+
+pytestmark = pytest.mark.gpu
+
+WIDE_F = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=4, head_dim=128, ffn_dim=12800,
+                            vocab=1003, dtype="bf16")
+F16_D64 = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=4, head_dim=64, ffn_dim=512,
+                             vocab=1003, dtype="f16")
+
+
+@pytest.mark.parametrize("model,cap,edges", [
+    (WIDE_F, 2200, [0, 1, 31, 32, 33, 1023, 1024, 1056, 2047, 2048, 2199]),
+    (replace(WIDE_F, dtype="f16"), 4200, [159, 160, 161, 3071, 3072, 3073, 4199]),
+    (F16_D64, 3000, [0, 127, 1025, 2999])])
+def test_alone_and_in_a_batch_the_same_bits(model, cap, edges):
+    B = 63
+    w = configs.custom(model, [1], [0], [1], index=86)
+    hw = inputs.make_weights(w, norm="random", bias=True)
+    kv_len = np.resize(np.array(edges, np.int32), B)
+    dec = inputs.make_decode(w, batch=B, kv_len=kv_len, cap=cap)
+    dm = DeviceModel(hw, cap + 1)
+    ck, cv = to_device(dec.cache_k, dm.device), to_device(dec.cache_v, dm.device)
+    lens, ids = to_device(dec.kv_len, dm.device), to_device(dec.token_ids, dm.device)
+
+    def step(rows):
+        logits = torch.empty((len(rows), model.vocab), dtype=torch.float32, device=dm.device)
+        nxt = dm.decode(ck[:, rows].contiguous(), cv[:, rows].contiguous(), lens[rows].contiguous(),
+                        ids[rows].contiguous(), logits=logits)
+        return logits, nxt
+
+    lg, nx = step(list(range(B)))
+    assert torch.isfinite(lg).all()
+    assert torch.equal(nx.long(), lg.argmax(1))
+    for b in range(len(edges)):
+        print("alone", int(kv_len[b]), flush=True)
+        l1, n1 = step([b])
+        assert torch.equal(l1[0], lg[b]) and int(n1[0]) == int(nx[b])
+    n = min(4, len(edges))
+    lo = oracle.decode_step(hw.as_f32(), model, inputs.to_f32(dec.cache_k[:, :n]), inputs.to_f32(dec.cache_v[:, :n]),
+                            dec.kv_len[:n], dec.token_ids[:n])[0]
+    # 16-bit decode logits of two layers: 2e-2, the bound of the decode parity tests
+    assert max_abs(lg[:n].cpu().numpy(), lo) <= 2e-2
+    dm.close()
