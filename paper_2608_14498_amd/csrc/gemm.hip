@@ -131,7 +131,7 @@ __device__ __forceinline__ void gemm_epilogue_lse(const GemmArgs& g, f32x16_t (&
   for (int i = 0; i < MI; ++i) {
     const int m = tm * GB_M + wm * TM + i * 32 + fr;
     const int mc = min(m, g.M - 1);
-    const int id = min(max(g.lse.ids[mc], 0), g.N - 1);
+    const int id = min(max(g.lse.ids[mc], 0), g.n_all - 1) - g.n_off;
     float mx = -INFINITY;
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
@@ -151,7 +151,8 @@ __device__ __forceinline__ void gemm_epilogue_lse(const GemmArgs& g, f32x16_t (&
       }
     sum += __shfl_xor(sum, 32, kWave);
     if (fk == 0 && m < g.M)
-      *reinterpret_cast<float2*>(g.lse.lse + ((int64_t)m * g.n_part + tn * 2 + wn) * 2) = make_float2(ms, sum);
+      *reinterpret_cast<float2*>(g.lse.lse + ((int64_t)m * g.n_part + g.n_off / 128 + tn * 2 + wn) * 2) =
+          make_float2(ms, sum);
   }
 }
 
@@ -267,10 +268,10 @@ __global__ __launch_bounds__(WGM * 2 * 64) void k_gemm_bf16(GemmArgs g) {
   auto b_logical = [&](int r) -> int {
     if (EPI == EPI_SWIGLU) {  // per 128-row half: 64 gate rows then the matching 64 up rows
       const int w = r >> 7, c = r & 127;
-      const int f = min(tn * 128 + w * 64 + (c & 63), g.N - 1);
+      const int f = min(tn * 128 + w * 64 + (c & 63), g.N - 1) + g.n_off;
       return (c >= 64 ? g.B.n1 : 0) + f;
     }
-    return min(tn * GB_N + r, g.N - 1);
+    return min(tn * GB_N + r, g.N - 1) + g.n_off;
   };
   uint4 ra0, ra1, ra2, ra3, ra4, ra5, ra6, ra7, rb0, rb1, rb2, rb3, rb4, rb5, rb6, rb7;
 #define G_LDA(i_, kt_)                                                                                    \
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(WGM * 2 * 64) void k_gemm_bf16(GemmArgs g) {
       const int kr_ = (tid >> 5) + (NT / 32) * i_;                                                     \
       rb##i_ = *reinterpret_cast<const uint4*>((const T16*)g.B.b0 +                                    \
                                                (int64_t)(kbeg + (kt_) * GB_K + kr_) * g.ldb +          \
-                                               min(tn * GB_N + (tid & 31) * 8, g.N - 8));              \
+                                               min(tn * GB_N + (tid & 31) * 8, g.N - 8) + g.n_off);   \
     } else {                                                                                           \
       const int r_ = lr + (NT / 8) * i_;                                                               \
       rb##i_ = *reinterpret_cast<const uint4*>(brow<T16>(g.B, b_logical(r_), g.ldb) + kbeg + lc * 8 + \
@@ -468,9 +469,9 @@ void k_gemm_bf16_dma(GemmArgs g) {
   auto b_logical = [&](int r) -> int {
     if (EPI == EPI_SWIGLU) {  // per 128-row half: 64 gate rows then the matching 64 up rows
       const int w = r >> 7, cc = r & 127;
-      return (cc >= 64 ? g.B.n1 : 0) + min(tn * 128 + w * 64 + (cc & 63), g.N - 1);
+      return (cc >= 64 ? g.B.n1 : 0) + min(tn * 128 + w * 64 + (cc & 63), g.N - 1) + g.n_off;
     }
-    return min(tn * GB_N + r, g.N - 1);
+    return min(tn * GB_N + r, g.N - 1) + g.n_off;
   };
   uint32_t aoff[LOADS], boff[LOADS];
   __amdgpu_buffer_rsrc_t rsB[LOADS];
@@ -486,7 +487,7 @@ void k_gemm_bf16_dma(GemmArgs g) {
       const int kr = 2 * (wave * LOADS + i) + (lane >> 5);
       const int cb = (lane & 31) ^ swzt(kr);
       rsB[i] = rsB0;
-      boff[i] = 2u * ((uint32_t)(kbeg + kr) * (uint32_t)g.ldb + (uint32_t)min(tn * GB_N + cb * 8, g.N - 8));
+      boff[i] = 2u * ((uint32_t)(kbeg + kr) * (uint32_t)g.ldb + (uint32_t)(min(tn * GB_N + cb * 8, g.N - 8) + g.n_off));
     } else {
       const int br0 = b_logical(r0);
       const int seg = br0 < g.B.n1 ? 0 : br0 < g.B.n2 ? 1 : 2;
@@ -1098,6 +1099,62 @@ int32_t gemm_effective_splitk(rp_dtype dt, int32_t K, int32_t splitk) {
   return (K + k_chunk - 1) / k_chunk;
 }
 
+// A launch of 256x256 tiles pays for a whole round of 256 however few tiles the last one
+// holds.  Where that is dear, the 256x256 kernel takes the rows or the columns that fill its
+// rounds and the flexible tiles the rest, as a second launch (every output keeps its bits).
+// us, whole / cut: 7B down projection of 14229 rows (784 tiles, 3.06 rounds) 1800 / 1539,
+// gate/up of 1024 rows (592, 2.3) 258 / 241, lm_head of 1024 rows (2376, 9.3) 1017 / 992;
+// 32B down projection of 10000 rows 2600 / 2210.
+static bool cut_last_round(GemmArgs* g, GemmArgs* tail, int epi, int c_bytes) {
+  const int nt = epi == EPI_SWIGLU ? 128 : GB_N;  // output columns of a tile
+  const int64_t tm = (g->M + GB_M - 1) / GB_M, tn = (g->N + nt - 1) / nt;
+  const int64_t full = tm * tn / 256 * 256;
+  double best = gemm_cost_256(*g, epi, 1) * 0.97;  // below 3% the second launch is not worth it
+  GemmArgs head_best, tail_best;
+  bool found = false;
+  for (int rows = 0; rows < 2; ++rows) {
+    const int64_t keep = full / (rows ? tn : tm);  // tile rows (columns) of the head
+    if (keep < 1 || keep >= (rows ? tm : tn)) continue;
+    GemmArgs h = *g, t = *g;
+    if (rows) {
+      const int64_t m = keep * GB_M;
+      h.M = (int)m;
+      t.M = g->M - (int)m;
+      t.A = (const char*)g->A + m * g->lda * 2;
+      if (epi == EPI_LSE) {
+        t.lse.ids += m;
+        t.lse.lse += m * g->n_part * 2;
+        t.lse.tgt += m;
+      } else if (epi == EPI_ROPE) {
+        t.rope.q = (char*)g->rope.q + m * g->rope.hq * 2;
+        t.rope.k = (char*)g->rope.k + m * g->rope.hkv * 2;
+        t.rope.v = (char*)g->rope.v + m * g->rope.hkv * 2;
+        t.rope.cs = g->rope.cs + m * (g->rope.D / 2);
+      } else {
+        t.C = (char*)g->C + m * g->ldc * c_bytes;
+      }
+    } else {
+      const int64_t n = keep * nt;
+      h.N = (int)n;
+      t.N = g->N - (int)n;
+      t.n_off = (int)n;
+      if (epi != EPI_LSE && epi != EPI_ROPE) t.C = (char*)g->C + n * c_bytes;
+    }
+    const double cost = gemm_cost_256(h, epi, 1) + gemm_cost_flex(t, epi, 1) + 3000.;
+    if (cost < best) {
+      best = cost;
+      head_best = h;
+      tail_best = t;
+      found = true;
+    }
+  }
+  if (found) {
+    *g = head_best;
+    *tail = tail_best;
+  }
+  return found;
+}
+
 // The fused SwiGLU with K summed as split-K partials would be: at most 64 rows, two or three
 // chunks (what k_gemm_flex has the registers for).
 bool gemm_swiglu_chunks(rp_dtype dt, int32_t M, int32_t N, int32_t K, int32_t splitk) {
@@ -1136,6 +1193,7 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
   g.lse = lse ? *lse : LseOut{nullptr, nullptr, nullptr};
   g.rope = rope ? *rope : RopeOut{};
   g.n_part = lse_parts(N);
+  g.n_all = N;
   if (splitk < 1) splitk = 1;
   const int bk = half ? GB_K : GF_K;
   const int kblocks = (K + bk - 1) / bk;
@@ -1150,13 +1208,17 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
   // EPI_PARTIALS: the partials epilogue even for one split, and no reduction here
   const bool split = splitk > 1 || epi == EPI_PARTIALS;
   const int64_t b_rows = epi == EPI_SWIGLU ? (int64_t)B.n1 + N : N;
-  // An unsplit product of few columns gives the skinny kernel (128 columns a workgroup, two
-  // stages) few workgroups: its down projection of 64 prompt rows runs on 28.  The flexible
-  // tile's deeper ring then wins (same bits).
-  const bool flex = half && dma_setup(g, b_rows, epi == EPI_SWIGLU) &&
-                    flex_gemm_wanted(g, split ? -1 : (int)epi, splitk);
-  if (g.k_sum && !flex) return hipErrorInvalidValue;
-  if (half && skinny_setup(g, epi, split) && !(flex && !split && N <= 128 * 128)) {
+  const int fepi = split ? -1 : (int)epi;
+  const bool flex_ok = half && (epi != EPI_STORE || split) && dma_setup(g, b_rows, epi == EPI_SWIGLU);
+  if (g.k_sum && !flex_ok) return hipErrorInvalidValue;
+  const double cost_256 = g.k_sum ? 1e30 : gemm_cost_256(g, fepi, splitk);
+  const bool flex = flex_ok && gemm_cost_flex(g, fepi, splitk) < 0.9 * cost_256;
+  // Up to 64 rows the skinny kernel streams the weights with three workgroups of two stages
+  // per CU; where its launch is less than one such workgroup per CU, the flexible tile's deeper
+  // ring reads faster (same bits).  Of 48 rows, 7B shapes, us (with timing events), skinny /
+  // flexible: q/k/v in 3 splits (108 workgroups) 21 / 16, down in 8 (224) 44 / 36; a decode
+  // step's 504 and 448 workgroups: 15 / 19 and 36 / 38.
+  if (half && skinny_setup(g, epi, split) && !(flex && (int64_t)((N + 127) / 128) * splitk <= 256)) {
     // split: partials (summed by the caller, or by the reduction below); else C itself
     with_half16(dt, [&](auto tag_) {
       using H = decltype(tag_);
@@ -1165,12 +1227,14 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
       else
         launch_skinny<H>(s, g, 1, (float*)C, ldc, 0, epi == EPI_ADD_F32);
     });
-  } else if (flex && (epi != EPI_STORE || split)) {
-    const hipError_t em = launch_flex_gemm(s, dt, split ? -1 : (int)epi, g, splitk);
+  } else if (flex) {
+    const hipError_t em = launch_flex_gemm(s, dt, fepi, g, splitk);
     if (em != hipSuccess) return em;
   } else if (half) {
-    g.tiles_m = (M + GB_M - 1) / GB_M;
-    g.tiles_n = epi == EPI_SWIGLU ? (N + 127) / 128 : (N + GB_N - 1) / GB_N;
+    GemmArgs tail;
+    const bool cut = flex_ok && !split && cut_last_round(&g, &tail, epi, epi == EPI_SWIGLU ? 2 : 4);
+    g.tiles_m = (g.M + GB_M - 1) / GB_M;
+    g.tiles_n = epi == EPI_SWIGLU ? (g.N + 127) / 128 : (g.N + GB_N - 1) / GB_N;
     dim3 grid(g.tiles_m * g.tiles_n, splitk);
     with_half16(dt, [&](auto tag_) {
       using H = decltype(tag_);
@@ -1193,6 +1257,10 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
       else
         launch_half<EPI_ADD_F32, H>(s, g, grid, b_rows);
     });
+    if (cut) {
+      const hipError_t em = launch_flex_gemm(s, dt, epi, tail, 1);
+      if (em != hipSuccess) return em;
+    }
   } else {
     g.tiles_m = (M + GF_M - 1) / GF_M;
     g.tiles_n = (N + GF_N - 1) / GF_N;

@@ -22,6 +22,8 @@ struct GemmArgs {
   LseOut lse;        // EPI_LSE outputs
   int n_part;        // EPI_LSE column blocks per row
   RopeOut rope;      // EPI_ROPE outputs
+  int n_off = 0;     // first logical column: a launch may take columns n_off .. n_off + N - 1 of B
+  int n_all = 0;     // EPI_LSE: columns of the whole product
   int k_sum = 0;     // EPI_SWIGLU, at most 64 rows: K summed in chunks of k_sum (0: one chain)
 };
 
@@ -126,8 +128,8 @@ __device__ __forceinline__ void store_rows(const GemmArgs& g, const F32Out& out,
     // rotate-half partners D/2 columns away in the same staged row
     const RopeOut& ro = g.rope;
     const int half = ro.D >> 1;
-    const int c = ncol0 + 4 * k;
-    if (c < g.N) {
+    const int c = ncol0 + 4 * k + g.n_off;
+    if (c - g.n_off < g.N) {
       const int seg = c < ro.hq ? 0 : c < ro.hq + ro.hkv ? 1 : 2;
       const int cc = seg == 0 ? c : seg == 1 ? c - ro.hq : c - ro.hq - ro.hkv;  // column in its segment
       const int64_t ld = seg == 0 ? ro.hq : ro.hkv;
@@ -235,8 +237,10 @@ __device__ __forceinline__ void store_rows(const GemmArgs& g, const F32Out& out,
   }
 }
 
-// GEMM over small tiles (gemm_flex.hip).
-bool flex_gemm_wanted(const GemmArgs& g, int epi, int splitk);
+// GEMM over small tiles (gemm_flex.hip): the cost in ns of the best tile (and of the
+// 256x256 kernel), by which the dispatch picks.
+double gemm_cost_256(const GemmArgs& g, int epi, int splitk);
+double gemm_cost_flex(const GemmArgs& g, int epi, int splitk);
 hipError_t launch_flex_gemm(hipStream_t s, rp_dtype dt, int epi, const GemmArgs& g, int splitk);
 
 }  // namespace rp

@@ -59,8 +59,8 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
   const __amdgpu_buffer_rsrc_t rsB2 = __builtin_amdgcn_make_buffer_rsrc((void*)g.B.b2, 0, (int)0xFFFFFF00u, 0x00020000);
   auto b_logical = [&](int r) -> int {
     if (EPI == EPI_SWIGLU)  // a wave's 32 rows: 16 gate rows, then the matching 16 up rows
-      return ((r & 16) ? g.B.n1 : 0) + min((tn * SW + (r >> 5)) * 16 + (r & 15), g.N - 1);
-    return min(tn * NT + r, g.N - 1);
+      return ((r & 16) ? g.B.n1 : 0) + min((tn * SW + (r >> 5)) * 16 + (r & 15), g.N - 1) + g.n_off;
+    return min(tn * NT + r, g.N - 1) + g.n_off;
   };
   uint32_t aoff[LA], boff[LB];
   int ablk[LA];  // 8-row block each A copy fills
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
       const int kr = 4 * (wave * LB + i) + (lane >> 4);
       const int cb = (lane & 15) ^ swzx(kr);
       rsB[i] = rsB0;
-      boff[i] = 2u * ((uint32_t)(kbeg + kr) * (uint32_t)g.ldb + (uint32_t)min(tn * NT + cb * 8, g.N - 8));
+      boff[i] = 2u * ((uint32_t)(kbeg + kr) * (uint32_t)g.ldb + (uint32_t)(min(tn * NT + cb * 8, g.N - 8) + g.n_off));
     } else {
       const int r0 = (wave * LB + i) * 8, r = r0 + (lane >> 3);
       const int c = (lane & 7) ^ swz(r);
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
         const int row = u >> 1, hf = u & 1, m = mp + row;
         const uint8_t* st = block(row >> 5) + (row & 31) * 512;
         const int c0 = tn * NT + 4 * hf;
-        const int id = min(max(g.lse.ids[min(m, g.M - 1)], 0), g.N - 1);
+        const int id = min(max(g.lse.ids[min(m, g.M - 1)], 0), g.n_all - 1) - g.n_off;
         float mx = -INFINITY;
 #pragma unroll 4
         for (int q = 0; q < 16; ++q) {
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
         }
         sum += __shfl_xor(sum, 1, kWave);
         if (hf == 0 && m < g.M)
-          *reinterpret_cast<float2*>(g.lse.lse + ((int64_t)m * g.n_part + tn) * 2) = make_float2(ms, sum);
+          *reinterpret_cast<float2*>(g.lse.lse + ((int64_t)m * g.n_part + g.n_off / 128 + tn) * 2) = make_float2(ms, sum);
       }
     } else if constexpr (EPI == EPI_SWIGLU) {
       const bool vec = (g.ldc & 3) == 0 && ((uintptr_t)g.C & 7) == 0;
@@ -343,15 +343,19 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
 // stages, and a slab that comes from HBM is 1.0-1.5 us away: it fills its slabs at 55-65 GB/s
 // (a probe with the copies alone, 128x128 tiles: 58 GB/s a unit with 112 and with 256 units
 // busy, one to three slabs ahead; 97 when the operands sit in the Infinity Cache, 125 in
-// L2).  So a tile costs its slabs' bytes at that rate, 66 ns for 32 rows of A or of B, plus a
-// fill and an epilogue that grow with the tile, and a launch takes as many rounds of 256
-// tiles.  The 256x256 kernel moves the fewest bytes per product (1.2 us a slab, 15 us a
-// tile), and wins as soon as its rounds are full.  Measured, 7B shapes, us, 256x256 against
-// the tile picked here: down projection of 470 rows 342 / 116 (64 rows by 128), of 1024 367 /
-// 161; gate/up of 470 rows 163 / 142 (160 by 128, two workgroups a unit), of 48 rows 80 / 47
-// (64 by 160: 237 tiles, one round), of 130 rows 83 / 59 (160 by 160); q/k/v of 470 rows 80 /
-// 40; lm_head of 130 rows 252 / 234; K/V projection of 6249 rows 77 / 63 (256 by 128).  At
-// 1024 rows the gate/up (258 against 287) and at 600 the lm_head (652 / 770) stay there.
+// L2).  So a tile costs its slabs' bytes at that rate, 66 ns for 32 rows of A or of B (some
+// 15% more when all units copy), plus a fill and an epilogue that grow with the tile; a launch
+// takes as many rounds of 256 tiles, the last one by what it holds; and no launch is faster
+// than its weights and outputs at 5 TB/s.  The 256x256 kernel moves the fewest bytes per
+// product (1.2-1.45 us a slab, 12 us a tile) and wins when its rounds are full; a tenth of
+// margin keeps it where the model cannot tell.  Measured, 7B shapes, us, 256x256 / the tile
+// picked here: down projection of 470 rows 342 / 116 (64 rows by 128), of 800 340 / 142
+// (128 by 128), of 1641 345 / 249 (256 by 128), of 2500 360 / 340 (160 by 128, two workgroups
+// a unit); gate/up of 48 rows 80 / 52 (64 by 160: 237 tiles, one round), of 130 rows 88 / 64
+// (160 by 160), of 470 163 / 142 and of 800 255 / 218 (160 by 128, two a unit); q/k/v of 470
+// rows 80 / 40; lm_head of 130 rows 252 / 234, of 300 485 / 425; q/k/v of a decode step of 160
+// rows in 14 splits 22 / 20.  At 1024 rows the gate/up (258 against 288) and at 600 the
+// lm_head (652 / 770) stay there.
 struct FlexTile {
   int RF, SW, NS;
 };
@@ -359,36 +363,60 @@ constexpr FlexTile kFlexTiles[] = {{2, 4, 6}, {4, 4, 5}, {5, 4, 4}, {5, 4, 2}, {
 
 static int flex_cols(const GemmArgs& g, int epi, int SW) {
   return epi == EPI_SWIGLU ? (g.N + 16 * SW - 1) / (16 * SW)
-                           : epi == EPI_LSE ? g.n_part : (g.N + 32 * SW - 1) / (32 * SW);
+                           : epi == EPI_LSE ? (g.N + 255) / 256 * 2 : (g.N + 32 * SW - 1) / (32 * SW);
 }
 
-static int flex_pick(const GemmArgs& g, int epi, int splitk) {
-  const double kt = g.k_chunk / GB_K;
-  const int64_t big = (int64_t)((g.M + 255) / 256) * (epi == EPI_SWIGLU ? (g.N + 127) / 128 : (g.N + 255) / 256) * splitk;
-  double best = g.k_sum ? 1e30 : (double)((big + 255) / 256) * (kt * 1190. + 15000.);
-  int pick = -1;
+// Time in ns that HBM takes for B and the output, which no tile avoids.
+static double hbm_floor(const GemmArgs& g, int epi, int splitk) {
+  const double out = (double)g.M * g.N;
+  const double bytes = 2. * g.K * g.N * (epi == EPI_SWIGLU ? 2. : 1.) +
+                       (epi == -1 ? 5. * splitk * out : epi == EPI_SWIGLU || epi == EPI_ROPE ? 2. * out : epi == EPI_LSE ? 0. : 4. * out);
+  return bytes / 5000.;
+}
+
+double gemm_cost_256(const GemmArgs& g, int epi, int splitk) {
+  const int64_t tiles = (int64_t)((g.M + 255) / 256) * (epi == EPI_SWIGLU ? (g.N + 127) / 128 : (g.N + 255) / 256) * splitk;
+  const double kt = g.k_chunk / GB_K, full = (double)(tiles / 256), rem = (double)(tiles % 256);
+  const double t = full * (kt * 1426. + 12000.) + (rem > 0 ? kt * (1170. + rem) + 12000. : 0.);
+  return std::max(t, hbm_floor(g, epi, splitk));
+}
+
+static int flex_pick(const GemmArgs& g, int epi, int splitk, double* best) {
+  const double kt = g.k_chunk / GB_K, floor = hbm_floor(g, epi, splitk);
+  int pick = 0;
+  double least = 1e30;
   for (int i = 0; i < (int)(sizeof kFlexTiles / sizeof kFlexTiles[0]); ++i) {
     const FlexTile& f = kFlexTiles[i];
     if (f.SW != 4 && epi != EPI_SWIGLU) continue;
     if (g.k_sum && f.RF > 2) continue;
     const int64_t tiles = (int64_t)((g.M + 32 * f.RF - 1) / (32 * f.RF)) * flex_cols(g, epi, f.SW) * splitk;
-    double slab = 66. * (f.RF + f.SW);
-    if (f.SW == 5) slab = std::max(slab, 170. * f.RF);  // five waves on four SIMDs: the MFMAs of two
-    double rounds = (double)((tiles + 255) / 256);
-    if (f.NS == 2) {  // two workgroups a unit: pays only where most units have both
+    const double full = (double)(tiles / 256), rem = (double)(tiles % 256);
+    double t;
+    if (f.NS == 2) {
+      // two workgroups a unit: pays where most units have both; beyond a few rounds they drift
+      // apart and the launch ends evenly
       if (tiles <= 256) continue;
-      rounds = (double)((tiles + 127) / 128) * 0.5;
+      const double rounds = tiles < 2048 ? 2. * (double)((tiles + 511) / 512) : tiles / 256. + 0.1;
+      t = rounds * (kt * 580. + 4300.);
+    } else {
+      double slab = 66. * (f.RF + f.SW), tile = 2000. + 215. * f.RF * f.SW;
+      if (f.SW == 5) slab = std::max(slab, 170. * f.RF);  // five waves on four SIMDs: the MFMAs of two
+      t = full * (kt * slab * 1.05 + tile) + (rem > 0 ? kt * slab * (0.9 + 0.15 * rem / 256.) + tile : 0.);
     }
-    const double cost = rounds * (kt * slab + 2000. + 215. * f.RF * f.SW);
-    if (cost < best) {
-      best = cost;
+    if (t < least) {
+      least = t;
       pick = i;
     }
   }
+  *best = std::max(least, floor);
   return pick;
 }
 
-bool flex_gemm_wanted(const GemmArgs& g, int epi, int splitk) { return flex_pick(g, epi, splitk) >= 0; }
+double gemm_cost_flex(const GemmArgs& g, int epi, int splitk) {
+  double c;
+  flex_pick(g, epi, splitk, &c);
+  return c;
+}
 
 template <typename T16, int RF, int SW, int NS>
 static void launch_flex_t(hipStream_t s, int epi, GemmArgs g, int splitk) {
@@ -423,7 +451,8 @@ static void launch_flex_t(hipStream_t s, int epi, GemmArgs g, int splitk) {
 }
 
 hipError_t launch_flex_gemm(hipStream_t s, rp_dtype dt, int epi, const GemmArgs& g, int splitk) {
-  const int pick = flex_pick(g, epi, splitk);
+  double cost;
+  const int pick = flex_pick(g, epi, splitk, &cost);
   with_half16(dt, [&](auto tag_) {
     using H = decltype(tag_);
     switch (pick) {
