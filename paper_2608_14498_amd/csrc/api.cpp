@@ -130,7 +130,8 @@ struct LayerWS {
   void* O;    // attention output [M, Hq*D]
   void* GU;   // [M, 2F]
   void* ACT;  // [M, F]
-  float* attn_part = nullptr;  // split-KV attention partials (suffix pass, 16-bit models)
+  float* attn_part = nullptr;  // key-chunk attention partials (suffix pass, 16-bit models)
+  int64_t attn_part_floats = 0;
 };
 
 // bf16 prefix/suffix layers fuse SwiGLU into the gate/up GEMM and need no [M, 2F] buffer.
@@ -378,6 +379,7 @@ size_t suffix_ws(const rp_model* m, int64_t R, uint32_t flags, int32_t splits, v
   carve_layer(c, m->cfg, R, true, !s->plan.fused, &s->L);
   const size_t np = rp::attn_partial_floats(R, m->cfg.n_q_heads, m->cfg.head_dim, splits);
   s->L.attn_part = np ? (float*)c.take(np * 4) : nullptr;
+  s->L.attn_part_floats = (int64_t)np;
   const int64_t kvrow = (int64_t)m->cfg.n_kv_heads * m->cfg.head_dim;
   s->Ks = c.take(R * kvrow * elem_size(m->cfg));
   s->Vs = c.take(R * kvrow * elem_size(m->cfg));
@@ -631,7 +633,11 @@ rp_status run_layer(const rp_model* m, hipStream_t s, const rp_layer_weights& lw
   a.Hkv = Hkv;
   a.D = D;
   a.scale = (float)(1.0 / sqrt((double)D));
-  a.part = w.attn_part;
+  a.long_keys = gemm_part != nullptr;  // the suffix pass
+  // (the GEMM partials are free between the q/k/v and the o projection)
+  const bool gp = (int64_t)plan.part_floats > w.attn_part_floats;
+  a.part = gp ? gemm_part : w.attn_part;
+  a.part_floats = gp ? (int64_t)plan.part_floats : w.attn_part_floats;
   RP_TRY_LAUNCH_N(nm.attn, rp::launch_attention(s, dt, st, a, M));
   const rp::BSeg bo = wo_operand(c, lw);
   if (s_o > 1) {
@@ -716,6 +722,9 @@ rp_status run_last_rows(const rp_model* m, hipStream_t s, const rp_layer_weights
   a.Hkv = Hkv;
   a.D = D;
   a.scale = (float)(1.0 / sqrt((double)D));
+  a.long_keys = true;
+  a.part = t.part;  // (free between the q and the o projection)
+  a.part_floats = (int64_t)t.plan.part_floats;
   RP_TRY_LAUNCH_N("prefix.tail_attention", rp::launch_attention(s, dt, tl, a, B));
   const rp::BSeg bo = wo_operand(c, lw);
   RP_TRY_LAUNCH_N("prefix.tail_gemm_o_proj", rp::launch_gemm(s, dt, B, d, hq, t.O, hq, bo, bo.trans ? d : hq, h_last, d,

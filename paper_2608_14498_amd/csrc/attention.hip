@@ -27,28 +27,28 @@
 namespace rp {
 
 struct QBlock {
-  int b, q_begin, q_end;  // query rows of this block (absolute rows)
+  int b, r_begin, r_end;  // rows of this block: P per query of sequence b, from its first query on
 };
 
 // Linear q-block index -> (sequence, block); blocks of a sequence are visited
-// last-first (the longest causal rows start first).
-__device__ __forceinline__ QBlock find_qblock(const SeqTable& st, int qbl, int BQ) {
+// last-first (the longest causal rows start first).  P rows per query.
+__device__ __forceinline__ QBlock find_qblock(const SeqTable& st, int qbl, int BQ, int P) {
   for (int b = 0; b < st.n; ++b) {
-    const int nq = st.q_cu[b + 1] - st.q_cu[b];
-    const int nb = (nq + BQ - 1) / BQ;
+    const int nr = (st.q_cu[b + 1] - st.q_cu[b]) * P;
+    const int nb = (nr + BQ - 1) / BQ;
     if (qbl < nb) {
       const int qb = nb - 1 - qbl;
       QBlock r;
       r.b = b;
-      r.q_begin = st.q_cu[b] + qb * BQ;
-      r.q_end = min(st.q_cu[b + 1], r.q_begin + BQ);
+      r.r_begin = qb * BQ;
+      r.r_end = min(nr, r.r_begin + BQ);
       return r;
     }
     qbl -= nb;
   }
   QBlock r;
   r.b = -1;
-  r.q_begin = r.q_end = 0;
+  r.r_begin = r.r_end = 0;
   return r;
 }
 
@@ -69,6 +69,20 @@ __device__ __forceinline__ QBlock find_qblock(const SeqTable& st, int qbl, int B
 // of the 8-byte chunks addressed by lanes i/4, i/4+4, i/4+8, i/4+12, so lane p
 // addressing V[k0 + p/4][d0 + 4(p%4)] hands lane i the four keys k0..k0+3 of head
 // dimension d0+i -- the MFMA operand, with no transposed copy of V.
+//
+// LONG (queries over a long first key segment: the suffix pass, the last rows of a prefix):
+//  - the rows of a block are (query, q head of one kv head) pairs, so that 48 responses'
+//    tokens of a 7-head group are 336 rows in 3 blocks, not 7 blocks of 48;
+//  - the sequence's keys are cut into attn_chunks() chunks with a softmax of their own, merged
+//    in order by fa_merge.  A workgroup takes one chunk and leaves its partial to
+//    k_attn_split_merge (few blocks: the chip needs the parallelism), or all of them, merged in
+//    registers (many blocks: partials of 128 queries x 28 heads are 2 KB a row and chunk).
+//    Both give the same bits, so the launch may choose by the whole batch.
+// A layer's attention, 7B shapes, us with timing events, before / now: 48 queries over 1501
+// keys 36 / 23, the last rows of 1200, 2048 and 3001 keys (fp16) 63 / 24, both bound by a few
+// key tiles in a row and two launches; 4 x 256 over 4096 99 / 99, 16 responses of 64 .. 1000
+// over 4096 and 8190 keys 692 / 692 (890 TFLOP/s).  Waves without a row compute all the same:
+// a branch round them cost the full blocks 2 to 5%.
 // ------------------------------------------------------------------------------------
 // Block -> (q block, q head), XCD-aware.  Workgroup i runs on XCD i % 8, which has its
 // own L2, so the q heads that share a kv head (one GQA group, reading the same K/V
@@ -134,12 +148,24 @@ __device__ __forceinline__ int kswz(int key) { return D == 128 ? (key & 15) : (k
 template <int D>
 __device__ __forceinline__ int vswz(int key) { return D == 128 ? (key & 3) << 2 : (key & 3) << 1; }
 
-template <typename T16, int D, int QW, int KT, int NW = 4>
+__device__ __forceinline__ void fa_merge_weights(float& M, float& L, float m, float l, float* wa, float* wb) {
+  const float mn = fmaxf(M, m);
+  *wa = __builtin_amdgcn_exp2f(M - mn);
+  *wb = __builtin_amdgcn_exp2f(m - mn);
+  L = fmaf(l, *wb, L * *wa);
+  M = mn;
+}
+
+// kDense: a row per (query, head), one pass over the keys.  kLong: packed rows, one chunk of keys
+// a workgroup (of those that have several).  kLongFold: packed rows, all chunks, merged here.
+enum AttnForm { kDense, kLong, kLongFold };
+template <typename T16, int D, int QW, int KT, int NW, AttnForm FORM>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QW == 1 ? 2 : 1, QW == 1 ? 2 : 1)))
 void k_attn_bf16(SeqTable st, AttnArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // buffer resources exist only in the device pass
   typedef Half16<T16> H;
   typedef typename H::V8 V8;
+  constexpr bool LONG = FORM != kDense, FOLD = FORM == kLongFold;
   constexpr int BQ = NW * 32 * QW;
   constexpr int CH = D / 8;               // 16-byte chunks per K/V row
   constexpr int KSTEPS = D / 16;          // MFMA k-steps of S^T (over Dh)
@@ -152,21 +178,22 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int h, qbl;
-  fa_block(fa_map(a.Hq, a.Hkv), blockIdx.x, a.Hq, &qbl, &h);
-  QBlock qb = find_qblock(st, qbl, BQ);
+  const int G = a.Hq / a.Hkv, P = LONG ? G : 1;  // P rows per query; LONG: h is the kv head
+  fa_block(fa_map(LONG ? a.Hkv : a.Hq, a.Hkv), blockIdx.x, LONG ? a.Hkv : a.Hq, &qbl, &h);
+  QBlock qb = find_qblock(st, qbl, BQ, P);
   if (qb.b < 0) return;
   // Block-uniform values, moved to scalar registers (the sequence table is indexed
   // dynamically, which the compiler cannot prove uniform).
   const int b = __builtin_amdgcn_readfirstlane(qb.b);
-  qb.q_begin = __builtin_amdgcn_readfirstlane(qb.q_begin);
-  qb.q_end = __builtin_amdgcn_readfirstlane(qb.q_end);
-  const int G = a.Hq / a.Hkv, g = h / G;
+  qb.r_begin = __builtin_amdgcn_readfirstlane(qb.r_begin);
+  qb.r_end = __builtin_amdgcn_readfirstlane(qb.r_end);
+  const int g = LONG ? h : h / G;
   const int krow0 = __builtin_amdgcn_readfirstlane(st.k_beg(b));
   const int n0 = __builtin_amdgcn_readfirstlane(st.pos0(b));
   const int qrow0 = __builtin_amdgcn_readfirstlane(st.q_cu[b]);
   const int nq = __builtin_amdgcn_readfirstlane(st.q_cu[b + 1]) - qrow0;
-  const int qpos_first = n0 + (qb.q_begin - qrow0);
-  const int qpos_last = n0 + (qb.q_end - 1 - qrow0);
+  const int qpos_first = n0 + qb.r_begin / P;
+  const int qpos_last = n0 + (qb.r_end - 1) / P;
   // Key tiles: the first P0 tiles hold the n0 first-segment keys (the last of them may be
   // partial: its rows past n0 read as zeros and are masked), the rest the segment-1 keys
   // n0 .. qpos_last this block needs, from position n0 on.  No tile mixes the segments,
@@ -174,20 +201,21 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
   // kpos0(t).
   const int P0 = (n0 + KT - 1) / KT;
   auto kpos0 = [&](int t) { return t < P0 ? t * KT : n0 + (t - P0) * KT; };
-  // Tiles t_begin .. t_end-1 of this block.  Split-KV: a sequence with n0 first-segment
-  // keys has nsp = attn_splits(n0) splits; split sp takes its share of the P0 first-
-  // segment tiles, and the last split also the segment-1 tiles (the causal keys), so it
-  // is the longest and runs at blockIdx.y 0.  Every split holds at least one tile
-  // (P0 / nsp >= RP_ATTN_SPLIT_KEYS / KT).
-  int t_begin = 0, t_end = P0 + (qpos_last - n0 + KT) / KT, sp = 0;
-  const int nsp = a.part ? attn_splits(n0) : 1;
-  if ((int)blockIdx.y >= nsp) return;
-  if (nsp > 1) {
-    sp = nsp - 1 - (int)blockIdx.y;
-    const int per = (P0 + nsp - 1) / nsp;
-    t_begin = sp * per;
-    if (sp < nsp - 1) t_end = t_begin + per;
+  // Tiles t_begin .. t_end-1 of this block.  LONG: chunk c of nch is the first-segment tiles
+  // P0 c / nch .. P0 (c + 1) / nch (at least one each: a chunk is 256 keys or more), the last
+  // chunk also the segment-1 tiles (the causal keys): it is the longest and runs at
+  // blockIdx.y 0.
+  int t_begin = 0, t_end = P0 + (qpos_last - n0 + KT) / KT, chunk = 0;
+  const int nch = LONG ? attn_chunks(n0, nq, a.Hq, a.Hkv) : 1;
+  const bool split = FORM == kLong && nch > 1;
+  if (FORM == kLong && (int)blockIdx.y >= nch) return;
+  auto chunk_end = [&](int c) { return c + 1 < nch ? P0 * (c + 1) / nch : t_end; };
+  if (split) {
+    chunk = nch - 1 - (int)blockIdx.y;
+    t_begin = P0 * chunk / nch;
+    t_end = chunk_end(chunk);
   }
+  int fold_at = !FOLD || nch == 1 ? -1 : chunk_end(0);  // tile count at which a chunk is done
 
   // Key segments as buffer resources: segment 0 = the n0 prefix rows, segment 1 = the
   // nq rows of the queries; key kv of segment s is at byte (kv - start_s) * row_bytes.
@@ -245,10 +273,10 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
   int qpos[QW];
 #pragma unroll
   for (int qi = 0; qi < QW; ++qi) {
-    const int qrow_raw = qb.q_begin + (wave * QW + qi) * 32 + fr;
-    const int qrow = min(qrow_raw, qb.q_end - 1);
-    qpos[qi] = n0 + (qrow_raw - qrow0);
-    const T16* qp = (const T16*)a.q + (int64_t)qrow * a.q_ld + h * D + fk * 8;
+    const int r_raw = qb.r_begin + (wave * QW + qi) * 32 + fr;
+    const int r = min(r_raw, qb.r_end - 1), q = r / P;
+    qpos[qi] = n0 + r_raw / P;
+    const T16* qp = (const T16*)a.q + (int64_t)(qrow0 + q) * a.q_ld + (h * P + r - q * P) * D + fk * 8;
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) qf[qi][ks] = H::as_v8(*reinterpret_cast<const uint4*>(qp + ks * 16));
   }
@@ -264,6 +292,39 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[qi][db][e] = 0.f;
   }
+  // FOLD: the merged chunks so far
+  f32x16_t ot[FOLD ? QW : 1][FOLD ? DB : 1];
+  float m_tot[QW], l_tot[QW];
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int qi = 0; qi < QW; ++qi) {
+      m_tot[qi] = kMaskVal;
+      l_tot[qi] = 0.f;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) ot[qi][db][e] = 0.f;
+    }
+  }
+  auto fold = [&]() __attribute__((always_inline)) {
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int qi = 0; qi < QW; ++qi) {
+        float wa, wb;
+        fa_merge_weights(m_tot[qi], l_tot[qi], m_run[qi], l_run[qi] + __shfl_xor(l_run[qi], 32, kWave), &wa, &wb);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            ot[qi][db][e] = fmaf(o[qi][db][e], wb, ot[qi][db][e] * wa);
+            o[qi][db][e] = 0.f;
+          }
+        m_run[qi] = kMaskVal;
+        l_run[qi] = 0.f;
+      }
+      fold_at = chunk_end(++chunk);
+    }
+  };
   const float c2 = a.scale * 1.4426950408889634f;  // scores in log2 units
   // V^T fragment addressing (see header): 16-lane group -> d0, lane p = lane % 16
   const int tr_p = lane & 15;
@@ -371,6 +432,7 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
   auto tile = [&](const u32x4_t* Kc, const u32x4_t* Vc, u32x4_t* Kn, u32x4_t* Vn, int t) __attribute__((always_inline)) {
     if (t + 1 < t_end) FA_LOAD(Kn, Vn, t + 1);
     compute(Kc, Vc, t);
+    if (FOLD && t + 1 == fold_at) fold();
     __syncthreads();
   };
   FA_LOAD(Ks0, Vs0, t_begin);
@@ -386,15 +448,15 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
 #undef FA_LOAD
 
   // ---- normalise and store: o[qi][db][e] = O^T(dh = db*32 + 8(e/4) + 4 fk + e%4, query fr) ----
-  if (nsp > 1) {  // split partial: (max in log2 units, sum, unnormalised o)
+  if (split) {  // partial of one chunk: (max in log2 units, sum, unnormalised o)
 #pragma unroll
     for (int qi = 0; qi < QW; ++qi) {
-      const int qrow = qb.q_begin + (wave * QW + qi) * 32 + fr;
+      const int r = qb.r_begin + (wave * QW + qi) * 32 + fr, q = r / P;
       const float l = l_run[qi] + __shfl_xor(l_run[qi], 32, kWave);
-      if (qrow >= qb.q_end) continue;
-      float* pp = a.part + ((int64_t)qrow * a.Hq + h) * attn_part_record(gridDim.y, D);
-      if (fk == 0) *reinterpret_cast<float2*>(pp + gridDim.y * D + 2 * sp) = make_float2(m_run[qi], l);
-      pp += sp * D;
+      if (r >= qb.r_end) continue;
+      float* pp = a.part + ((int64_t)(qrow0 + q) * a.Hq + h * P + r - q * P) * attn_part_record(gridDim.y, D);
+      if (fk == 0) *reinterpret_cast<float2*>(pp + gridDim.y * D + 2 * chunk) = make_float2(m_run[qi], l);
+      pp += chunk * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -406,21 +468,29 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
   }
 #pragma unroll
   for (int qi = 0; qi < QW; ++qi) {
-    const int qrow = qb.q_begin + (wave * QW + qi) * 32 + fr;
-    const float l = l_run[qi] + __shfl_xor(l_run[qi], 32, kWave);
-    if (qrow >= qb.q_end) continue;
+    const int r = qb.r_begin + (wave * QW + qi) * 32 + fr, q = r / P;
+    float l = l_run[qi] + __shfl_xor(l_run[qi], 32, kWave);
+    if constexpr (FOLD) {
+      if (nch > 1) l = l_tot[qi];  // (the last chunk was folded at t_end)
+    }
+    if (r >= qb.r_end) continue;
     const float inv = 1.0f / l;
-    T16* op = (T16*)a.o + (int64_t)qrow * a.Hq * D + h * D;
+    T16* op = (T16*)a.o + (int64_t)(qrow0 + q) * a.Hq * D + (h * P + r - q * P) * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; ++db) {
+      f32x16_t v = o[qi][db];
+      if constexpr (FOLD) {
+        if (nch > 1) v = ot[qi][db];
+      }
 #pragma unroll
       for (int e4 = 0; e4 < 4; ++e4) {
         const int dh = db * 32 + 8 * e4 + 4 * fk;
         uint2 w;
-        w.x = H::pack2(o[qi][db][4 * e4] * inv, o[qi][db][4 * e4 + 1] * inv);
-        w.y = H::pack2(o[qi][db][4 * e4 + 2] * inv, o[qi][db][4 * e4 + 3] * inv);
+        w.x = H::pack2(v[4 * e4] * inv, v[4 * e4 + 1] * inv);
+        w.y = H::pack2(v[4 * e4 + 2] * inv, v[4 * e4 + 3] * inv);
         *reinterpret_cast<uint2*>(op + dh) = w;
       }
+    }
   }
 #endif
 }
@@ -447,18 +517,18 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(SeqTable st, AttnArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = lane & 31, fk = lane >> 5;
   const int h = blockIdx.x % a.Hq;
-  QBlock qb = find_qblock(st, blockIdx.x / a.Hq, BQ);
+  QBlock qb = find_qblock(st, blockIdx.x / a.Hq, BQ, 1);
   if (qb.b < 0) return;
   const int b = __builtin_amdgcn_readfirstlane(qb.b);
-  qb.q_begin = __builtin_amdgcn_readfirstlane(qb.q_begin);
-  qb.q_end = __builtin_amdgcn_readfirstlane(qb.q_end);
+  qb.r_begin = __builtin_amdgcn_readfirstlane(qb.r_begin);
+  qb.r_end = __builtin_amdgcn_readfirstlane(qb.r_end);
   const int g = h / (a.Hq / a.Hkv);
   const int n0 = __builtin_amdgcn_readfirstlane(st.pos0(b));
   const int qrow0 = __builtin_amdgcn_readfirstlane(st.q_cu[b]);
   const int krow0 = __builtin_amdgcn_readfirstlane(st.k_beg(b));
-  const int qrow_raw = qb.q_begin + fr, qrow = min(qrow_raw, qb.q_end - 1);
+  const int qrow_raw = qrow0 + qb.r_begin + fr, qrow = min(qrow_raw, qrow0 + qb.r_end - 1);
   const int qi = qrow - qrow0;                     // this lane's query among its sequence's
-  const int nk1 = qb.q_end - qrow0;                // segment-1 keys this block needs
+  const int nk1 = qb.r_end;                        // segment-1 keys this block needs
   const int P0 = (n0 + KT - 1) / KT;               // no tile mixes the key segments
   const int ntiles = P0 + (nk1 + KT - 1) / KT;
   const int64_t kv_ld = (int64_t)a.Hkv * D;
@@ -587,7 +657,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(SeqTable st, AttnArgs a) {
     L += ml[w][lane].y * f[w];
   }
   const float inv = 1.0f / L;
-  if (qrow_raw >= qb.q_end) return;
+  if (qrow_raw >= qrow0 + qb.r_end) return;
   float* op = (float*)a.o + (int64_t)qrow * a.Hq * D + h * D + 4 * fk;
   for (int c = wave; c < DB * 4; c += NW) {
     float v[4] = {0.f, 0.f, 0.f, 0.f};
@@ -605,48 +675,64 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(SeqTable st, AttnArgs a) {
   }
 }
 
-// Merge of split-KV partials: one wave per (query row, q head), lane i holding head
-// dimensions i*D/64 ..; rows of sequences that did not split were written by the
-// attention kernel.  Partial s of (row, head) is at ((row*Hq + head)*S + s)*(D + 4):
-// max (log2 units), sum, two pad floats, unnormalised o[D].
+// Merge of chunk partials: one wave per (query row, q head), lane i holding head dimensions
+// i*D/64 ..; rows of sequences of one chunk were written by the attention kernel.  The o of
+// chunk c of (row, head) is at (row*Hq + head) * attn_part_record(S, D) + c*D, its (max in log2
+// units, sum) at S*D + 2c there.  The chunks are merged in order, as the attention kernel does
+// when it takes them all.
 template <typename T16, int D>
 __global__ __launch_bounds__(256) void k_attn_split_merge(SeqTable st, const float* __restrict__ part, int S, int Hq,
-                                                          int64_t items, T16* __restrict__ o) {
+                                                          int Hkv, int64_t items, T16* __restrict__ o) {
   typedef Half16<T16> H;
   constexpr int PER = D / 64;
   const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (item >= items) return;
   const int lane = threadIdx.x & 63;
-  const int nsp = attn_splits(st.pos0(seq_of_row(st, (int)(item / Hq))));
-  if (nsp == 1) return;
+  const int b = seq_of_row(st, (int)(item / Hq));
+  const int nch = attn_chunks(st.pos0(b), st.q_cu[b + 1] - st.q_cu[b], Hq, Hkv);
+  if (nch == 1) return;
   const float* p = part + item * attn_part_record(S, D);
   const float* ml = p + S * D;
-  float M = -INFINITY;
-  for (int sp = 0; sp < nsp; ++sp) M = fmaxf(M, ml[2 * sp]);
-  float L = 0.f, acc[PER];
+  float v[kAttnMaxSplits][PER], m[kAttnMaxSplits], l[kAttnMaxSplits];
+#pragma unroll
+  for (int c = 0; c < kAttnMaxSplits; ++c) {  // every load in flight at once
+    const int cc = min(c, nch - 1);
+    m[c] = ml[2 * cc];
+    l[c] = ml[2 * cc + 1];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) v[c][e] = p[cc * D + lane * PER + e];
+  }
+  float M = kMaskVal, L = 0.f, acc[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-  for (int sp = 0; sp < nsp; ++sp) {
-    const float w = __builtin_amdgcn_exp2f(ml[2 * sp] - M);
-    L = fmaf(ml[2 * sp + 1], w, L);
 #pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] = fmaf(p[sp * D + lane * PER + e], w, acc[e]);
+  for (int c = 0; c < kAttnMaxSplits; ++c) {
+    if (c >= nch) break;
+    float wa, wb;
+    fa_merge_weights(M, L, m[c], l[c], &wa, &wb);
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] = fmaf(v[c][e], wb, acc[e] * wa);
   }
   const float inv = 1.0f / L;
   T16* op = o + item * D + lane * PER;
-  if constexpr (PER == 2)
+  if constexpr (PER == 2) {
     *reinterpret_cast<uint32_t*>(op) = H::pack2(acc[0] * inv, acc[1] * inv);
-  else
-    stf(op, acc[0] * inv);
+  } else {
+    // rounded to fp32 first, as the attention kernel's packed conversion does (a product and
+    // its conversion to fp16 otherwise become one instruction with one rounding)
+    float r = acc[0] * inv;
+    asm("" : "+v"(r));
+    stf(op, r);
+  }
 }
 
 size_t attn_partial_floats(int64_t R, int32_t Hq, int32_t D, int32_t max_splits) {
   return max_splits > 1 ? (size_t)R * Hq * attn_part_record(max_splits, D) : 0;
 }
 
-int count_qblocks(const SeqTable& st, int BQ) {
+int count_qblocks(const SeqTable& st, int BQ, int P = 1) {
   int n = 0;
-  for (int b = 0; b < st.n; ++b) n += (st.q_cu[b + 1] - st.q_cu[b] + BQ - 1) / BQ;
+  for (int b = 0; b < st.n; ++b) n += ((st.q_cu[b + 1] - st.q_cu[b]) * P + BQ - 1) / BQ;
   return n;
 }
 
@@ -655,9 +741,9 @@ int count_qblocks(const SeqTable& st, int BQ) {
 hipError_t launch_attention_variant(hipStream_t s, int variant, const SeqTable& st, const AttnArgs& a) {
   const FaMap m = fa_map(a.Hq, a.Hkv);
   if (variant == 0)
-    k_attn_bf16<bf16_t, 128, 1, 64><<<fa_grid(m, count_qblocks(st, 128), a.Hq), 256, 0, s>>>(st, a);
+    k_attn_bf16<bf16_t, 128, 1, 64, 4, kDense><<<fa_grid(m, count_qblocks(st, 128), a.Hq), 256, 0, s>>>(st, a);
   else
-    k_attn_bf16<bf16_t, 128, 2, 32><<<fa_grid(m, count_qblocks(st, 256), a.Hq), 256, 0, s>>>(st, a);
+    k_attn_bf16<bf16_t, 128, 2, 32, 4, kDense><<<fa_grid(m, count_qblocks(st, 256), a.Hq), 256, 0, s>>>(st, a);
   return hipGetLastError();
 }
 
@@ -669,41 +755,65 @@ hipError_t launch_attention(hipStream_t s, rp_dtype dt, const SeqTable& st, cons
       const int64_t keys = (int64_t)st.pos0(b) + (st.q_cu[b + 1] - st.q_cu[b]);
       if ((keys + 64) * a.Hkv * a.D * 2 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
     }
-    int S = 1;  // split-KV ways of the most split sequence (grid y)
-    if (a.part)
-      for (int b = 0; b < st.n; ++b) S = std::max(S, attn_splits(st.pos0(b)));
-    AttnArgs as = a;
-    if (S == 1) as.part = nullptr;
     hipError_t e = hipSuccess;
     with_half16(dt, [&](auto tag_) {
       using H = decltype(tag_);
-      // Long sequences: 8 waves (256 queries) share each K/V tile, halving the tile loads
-      // per query; shorter ones keep 4 waves, whose smaller blocks balance better (also
-      // measured faster for split suffix passes).  Each query sees the same key tiles in
-      // the same order either way (same results).
+      // Long sequences: 8 waves (256 rows) share each K/V tile, halving the tile loads
+      // per query; shorter ones keep 4 waves, whose smaller blocks balance better.  Each
+      // wave sees the same rows and key tiles in the same order either way (same results).
       int max_q = 0;
       for (int b = 0; b < st.n; ++b) max_q = std::max(max_q, st.q_cu[b + 1] - st.q_cu[b]);
-      const FaMap fm = fa_map(a.Hq, a.Hkv);
-      if (max_q >= 8192) {
-        const dim3 grid(fa_grid(fm, count_qblocks(st, 256), a.Hq), S);
-        if (a.D == 128)
-          k_attn_bf16<H, 128, 1, 64, 8><<<grid, 512, 0, s>>>(st, as);
-        else
-          k_attn_bf16<H, 64, 1, 64, 8><<<grid, 512, 0, s>>>(st, as);
-      } else {
-        const dim3 grid(fa_grid(fm, count_qblocks(st, 128), a.Hq), S);
-        if (a.D == 128)
-          k_attn_bf16<H, 128, 1, 64><<<grid, 256, 0, s>>>(st, as);
-        else
-          k_attn_bf16<H, 64, 1, 64><<<grid, 256, 0, s>>>(st, as);
+      const bool wide = max_q >= 8192;
+      const int BQ = wide ? 256 : 128;
+      if (a.long_keys) {
+        const int P = a.Hq / a.Hkv;
+        const int grid = fa_grid(fa_map(a.Hkv, a.Hkv), count_qblocks(st, BQ, P), a.Hkv);
+        // The chunks go to workgroups of their own while the blocks alone leave CUs short of
+        // the two workgroups that they hold and the partials fit the scratch memory at hand.
+        int chunks = 1;
+        for (int b = 0; b < st.n; ++b)
+          chunks = std::max(chunks, attn_chunks(st.pos0(b), st.q_cu[b + 1] - st.q_cu[b], a.Hq, a.Hkv));
+        const bool fit = a.part && (int64_t)attn_partial_floats(total_q, a.Hq, a.D, chunks) <= a.part_floats;
+        const bool fold = chunks > 1 && (grid >= 512 || !fit);
+        const int S = fold ? 1 : chunks;
+        const dim3 g(grid, S);
+        auto run = [&](auto d_, auto nw_) {
+          constexpr int D = decltype(d_)::value, NW = decltype(nw_)::value;
+          if (fold)
+            k_attn_bf16<H, D, 1, 64, NW, kLongFold><<<g, NW * 64, 0, s>>>(st, a);
+          else
+            k_attn_bf16<H, D, 1, 64, NW, kLong><<<g, NW * 64, 0, s>>>(st, a);
+        };
+        typedef std::integral_constant<int, 4> N4;
+        typedef std::integral_constant<int, 8> N8;
+        if (a.D == 128) {
+          typedef std::integral_constant<int, 128> D128;
+          wide ? run(D128{}, N8{}) : run(D128{}, N4{});
+        } else {
+          typedef std::integral_constant<int, 64> D64;
+          wide ? run(D64{}, N8{}) : run(D64{}, N4{});
+        }
+        if (S > 1 && (e = hipGetLastError()) == hipSuccess) {
+          const int64_t items = (int64_t)total_q * a.Hq;
+          const int mgrid = (int)((items + 3) / 4);
+          if (a.D == 128)
+            k_attn_split_merge<H, 128><<<mgrid, 256, 0, s>>>(st, a.part, S, a.Hq, a.Hkv, items, (H*)a.o);
+          else
+            k_attn_split_merge<H, 64><<<mgrid, 256, 0, s>>>(st, a.part, S, a.Hq, a.Hkv, items, (H*)a.o);
+        }
+        return;
       }
-      if (S > 1 && (e = hipGetLastError()) == hipSuccess) {
-        const int64_t items = (int64_t)total_q * a.Hq;
-        const int mgrid = (int)((items + 3) / 4);
-        if (a.D == 128)
-          k_attn_split_merge<H, 128><<<mgrid, 256, 0, s>>>(st, as.part, S, a.Hq, items, (H*)a.o);
+      const int grid = fa_grid(fa_map(a.Hq, a.Hkv), count_qblocks(st, BQ), a.Hq);
+      if (a.D == 128) {
+        if (wide)
+          k_attn_bf16<H, 128, 1, 64, 8, kDense><<<grid, 512, 0, s>>>(st, a);
         else
-          k_attn_split_merge<H, 64><<<mgrid, 256, 0, s>>>(st, as.part, S, a.Hq, items, (H*)a.o);
+          k_attn_bf16<H, 128, 1, 64, 4, kDense><<<grid, 256, 0, s>>>(st, a);
+      } else {
+        if (wide)
+          k_attn_bf16<H, 64, 1, 64, 8, kDense><<<grid, 512, 0, s>>>(st, a);
+        else
+          k_attn_bf16<H, 64, 1, 64, 4, kDense><<<grid, 256, 0, s>>>(st, a);
       }
     });
     if (e != hipSuccess) return e;

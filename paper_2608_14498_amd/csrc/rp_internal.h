@@ -196,17 +196,18 @@ struct AttnArgs {
   void* o;
   int32_t Hq, Hkv, D;
   float scale;
-  // Split-KV (16-bit models): when set, a sequence whose first key segment holds n0 rows
-  // splits its keys attn_splits(n0) ways; the splits write (max, sum, unnormalised o)
-  // partials here and a merge kernel writes o.  attn_partial_floats() floats: one record
-  // of attn_part_record(S, D) floats per (query row, head) for a launch of S split slots,
-  // split sp's o at sp * D and its (max, sum) at S * D + 2 sp, so each split's o is whole
-  // 128-byte lines written by one workgroup.
+  // 16-bit models, queries over a long first key segment (suffix pass, last rows of a prefix):
+  // pack the q heads of a kv head into the query blocks and cut a sequence's keys into
+  // attn_chunks() chunks.  part (part_floats floats of scratch, may be null) lets a launch of
+  // few blocks give each chunk a workgroup: one record of attn_part_record(S, D) floats per
+  // (query row, head) for S chunk slots, chunk c's unnormalised o at c * D and its (max, sum)
+  // at S * D + 2 c, so each chunk's o is whole 128-byte lines written by one workgroup.
+  bool long_keys = false;
   float* part = nullptr;
+  int64_t part_floats = 0;
 };
 __host__ __device__ inline int attn_part_record(int S, int D) { return S * D + 32; }
-// Key splits of a sequence with n0 first-segment keys: a function of n0 alone, so a
-// sequence's result does not depend on the sequences packed with it.
+// Scratch set aside for chunk partials: this many ways for a first segment of n0 keys.
 #ifndef RP_ATTN_SPLIT_KEYS
 #define RP_ATTN_SPLIT_KEYS 4096
 #endif
@@ -214,6 +215,22 @@ constexpr int kAttnMaxSplits = 8;
 __host__ __device__ inline int attn_splits(int n0) {
   const int sp = n0 / RP_ATTN_SPLIT_KEYS;
   return sp < 1 ? 1 : (sp > kAttnMaxSplits ? kAttnMaxSplits : sp);
+}
+// Key chunks of a sequence of nq queries over n0 first-segment keys: a function of the sequence
+// and the head counts alone, so its result does not depend on the sequences packed with it.
+// As many as bring the sequence to about 64 workgroups, of 256 keys or more: 48 queries over
+// 1501 keys (7B heads) run 36 -> 23 us a layer.  Aiming at 128 cut 4 responses of 256 tokens in
+// two and left them at 100 us (two workgroups on a CU each run at little over half speed).
+// Long segments are cut whatever the queries.  At most 7, since partials of 7 chunks fit the
+// memory of a down projection's partials.
+__host__ __device__ inline int attn_chunks(int n0, int nq, int Hq, int Hkv) {
+  if (nq <= 0) return 1;  // an empty response
+  const int blocks = (nq * (Hq / Hkv) + 127) / 128 * Hkv;
+  int c = (64 + blocks / 2) / blocks;
+  c = c < n0 / 256 ? c : n0 / 256;
+  c = c < 7 ? c : 7;
+  const int least = attn_splits(n0);
+  return c > least ? c : least;
 }
 // Partial floats for R query rows whose sequences split at most max_splits ways.
 size_t attn_partial_floats(int64_t R, int32_t Hq, int32_t D, int32_t max_splits);
