@@ -267,9 +267,11 @@ int decode_splitk(const rp_config& cfg, int32_t M, int32_t N, int32_t K) {
 // Split-K plan of one decoder layer's GEMMs.
 //   prefix: no split (the prefix holds many rows; results are bitwise independent of how
 //           sequences are packed);
-//   suffix: GEMMs with fewer than 16384 output columns split K into min(8, K/1024) chunks,
+//   suffix: GEMMs with fewer than 16384 output columns split K into min(4, K/1024) chunks,
 //           a factor that depends on the shapes of the weights only, so a row's result
-//           does not depend on how many other rows share the launch;
+//           does not depend on how many other rows share the launch.  8 chunks of the 7B down
+//           projection wrote twice the partials: 1024 rows 149 us, 4 chunks 125 (and 3 in the
+//           norm that sums them), 6727 rows 1006 / 859, 48 rows 35 / 37;
 //   decode: split to fill the chip for the batch at hand (decode_splitk).
 // Split GEMMs cannot fuse SwiGLU into their epilogue.
 enum class Pass { kPrefix, kSuffix, kDecode };
@@ -278,10 +280,10 @@ struct LayerPlan {
   bool fused = false;
   size_t part_floats = 0;
 };
-int suffix_splitk(const rp_config& cfg, int32_t N, int32_t K) {
+int suffix_splitk(const rp_config& cfg, int32_t N, int32_t K, int most = 4) {
   if (!half_dtype(cfg) || N >= 16384) return 1;
   int s = K / 1024;
-  return s < 1 ? 1 : s > 8 ? 8 : s;
+  return s < 1 ? 1 : s > most ? most : s;
 }
 LayerPlan plan_layer(const rp_config& c, int32_t M, Pass pass) {
   const int d = c.d_model, F = c.ffn_dim, qkv = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
@@ -295,9 +297,11 @@ LayerPlan plan_layer(const rp_config& c, int32_t M, Pass pass) {
   p.gu = f(2 * F, d);
   p.down = f(d, F);
   p.fused = half_dtype(c) && p.gu == 1;
-  const int64_t shapes[4][3] = {{qkv, p.qkv, 0}, {d, p.o, 0}, {2 * F, p.gu, 0}, {d, p.down, 0}};
+  const int64_t shapes[4][3] = {{qkv, p.qkv, d}, {d, p.o, hq}, {2 * F, p.gu, d}, {d, p.down, F}};
   for (auto& sh : shapes) {
-    const size_t fl = rp::gemm_partial_floats(M, (int32_t)sh[0], (int32_t)sh[1]);
+    // suffix: room for 8 chunks (the attention's partials use it too)
+    const int ways = pass == Pass::kSuffix ? suffix_splitk(c, (int)sh[0], (int)sh[2], 8) : (int)sh[1];
+    const size_t fl = rp::gemm_partial_floats(M, (int32_t)sh[0], ways);
     p.part_floats = fl > p.part_floats ? fl : p.part_floats;
   }
   return p;

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
   constexpr int NREAD = RF + (BT ? 2 : 1);      // LDS reads per k-step
   constexpr uint32_t kOob = 0xFFFFFFF0u;        // past every resource's extent: nothing is fetched
   static_assert(NS >= 2 && NS <= 6 && (NS - 1) * L <= 63, "ring");
-  static_assert(SW == 4 || (!BT && EPI != EPI_ROPE && EPI != EPI_LSE), "128-column tiles");
+  static_assert(SW == 4 || (!BT && EPI == (SW == 2 ? -1 : (int)EPI_SWIGLU)), "128-column tiles");
   __shared__ u32x4_t S0[SC], S1[SC];
   __shared__ u32x4_t S2[NS > 2 ? SC : 1], S3[NS > 3 ? SC : 1], S4[NS > 4 ? SC : 1], S5[NS > 5 ? SC : 1];
 
@@ -356,10 +356,14 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_flex(GemmArgs g) {
 // rows 80 / 40; lm_head of 130 rows 252 / 234, of 300 485 / 425; q/k/v of a decode step of 160
 // rows in 14 splits 22 / 20.  At 1024 rows the gate/up (258 against 288) and at 600 the
 // lm_head (652 / 770) stay there.
+// Partials of few rows take 64 by 64 where 128 columns give too few workgroups: 48 rows, with
+// timing events, 128 / 64 columns: down in 4 splits (112 / 224 workgroups) 47 / 37, q/k/v in 3
+// 17 / 13, o 15 / 13.
 struct FlexTile {
   int RF, SW, NS;
 };
-constexpr FlexTile kFlexTiles[] = {{2, 4, 6}, {4, 4, 5}, {5, 4, 4}, {5, 4, 2}, {8, 4, 3}, {2, 5, 5}, {4, 5, 4}, {5, 5, 4}};
+constexpr FlexTile kFlexTiles[] = {{2, 4, 6}, {4, 4, 5}, {5, 4, 4}, {5, 4, 2}, {8, 4, 3}, {2, 5, 5},
+                                   {4, 5, 4}, {5, 5, 4}, {2, 2, 6}};
 
 static int flex_cols(const GemmArgs& g, int epi, int SW) {
   return epi == EPI_SWIGLU ? (g.N + 16 * SW - 1) / (16 * SW)
@@ -387,7 +391,8 @@ static int flex_pick(const GemmArgs& g, int epi, int splitk, double* best) {
   double least = 1e30;
   for (int i = 0; i < (int)(sizeof kFlexTiles / sizeof kFlexTiles[0]); ++i) {
     const FlexTile& f = kFlexTiles[i];
-    if (f.SW != 4 && epi != EPI_SWIGLU) continue;
+    if (f.SW == 5 && epi != EPI_SWIGLU) continue;
+    if (f.SW == 2 && (epi != -1 || g.B.trans)) continue;
     if (g.k_sum && f.RF > 2) continue;
     const int64_t tiles = (int64_t)((g.M + 32 * f.RF - 1) / (32 * f.RF)) * flex_cols(g, epi, f.SW) * splitk;
     const double full = (double)(tiles / 256), rem = (double)(tiles % 256);
@@ -423,14 +428,18 @@ static void launch_flex_t(hipStream_t s, int epi, GemmArgs g, int splitk) {
   g.tiles_m = (g.M + 32 * RF - 1) / (32 * RF);
   g.tiles_n = flex_cols(g, epi, SW);
   const dim3 grid(g.tiles_m * g.tiles_n, splitk);
-  if constexpr (RF == 2)
+  if constexpr (SW == 2) {
+    k_gemm_flex<-1, T16, RF, SW, NS><<<grid, SW * 64, 0, s>>>(g);
+    return;
+  }
+  if constexpr (RF == 2 && SW != 2)
     if (g.k_sum) {
       k_gemm_flex<EPI_SWIGLU, T16, RF, SW, NS, false, true><<<grid, SW * 64, 0, s>>>(g);
       return;
     }
-  if constexpr (SW != 4) {
+  if constexpr (SW == 5) {
     k_gemm_flex<EPI_SWIGLU, T16, RF, SW, NS><<<grid, SW * 64, 0, s>>>(g);
-  } else {
+  } else if constexpr (SW == 4) {
     if (g.B.trans && epi == -1)
       k_gemm_flex<-1, T16, RF, SW, NS, true><<<grid, SW * 64, 0, s>>>(g);
     else if (g.B.trans)
@@ -463,7 +472,8 @@ hipError_t launch_flex_gemm(hipStream_t s, rp_dtype dt, int epi, const GemmArgs&
       case 4: launch_flex_t<H, 8, 4, 3>(s, epi, g, splitk); break;
       case 5: launch_flex_t<H, 2, 5, 5>(s, epi, g, splitk); break;
       case 6: launch_flex_t<H, 4, 5, 4>(s, epi, g, splitk); break;
-      default: launch_flex_t<H, 5, 5, 4>(s, epi, g, splitk); break;
+      case 7: launch_flex_t<H, 5, 5, 4>(s, epi, g, splitk); break;
+      default: launch_flex_t<H, 2, 2, 6>(s, epi, g, splitk); break;
     }
   });
   return hipGetLastError();
