@@ -130,8 +130,6 @@ struct LayerWS {
   void* O;    // attention output [M, Hq*D]
   void* GU;   // [M, 2F]
   void* ACT;  // [M, F]
-  float* attn_part = nullptr;  // key-chunk attention partials (suffix pass, 16-bit models)
-  int64_t attn_part_floats = 0;
 };
 
 // bf16 prefix/suffix layers fuse SwiGLU into the gate/up GEMM and need no [M, 2F] buffer.
@@ -278,6 +276,7 @@ enum class Pass { kPrefix, kSuffix, kDecode };
 struct LayerPlan {
   int qkv = 1, o = 1, gu = 1, down = 1;
   bool fused = false;
+  int attn_chunks = 1;  // most key chunks of a sequence (suffix)
   size_t part_floats = 0;
 };
 int suffix_splitk(const rp_config& cfg, int32_t N, int32_t K, int most = 4) {
@@ -298,11 +297,21 @@ LayerPlan plan_layer(const rp_config& c, int32_t M, Pass pass) {
   p.down = f(d, F);
   p.fused = half_dtype(c) && p.gu == 1;
   const int64_t shapes[4][3] = {{qkv, p.qkv, d}, {d, p.o, hq}, {2 * F, p.gu, d}, {d, p.down, F}};
+  size_t row = 0;  // floats a row of eight K splits
   for (auto& sh : shapes) {
-    // suffix: room for 8 chunks (the attention's partials use it too)
-    const int ways = pass == Pass::kSuffix ? suffix_splitk(c, (int)sh[0], (int)sh[2], 8) : (int)sh[1];
-    const size_t fl = rp::gemm_partial_floats(M, (int32_t)sh[0], ways);
-    p.part_floats = fl > p.part_floats ? fl : p.part_floats;
+    p.part_floats = std::max(p.part_floats, rp::gemm_partial_floats(M, (int32_t)sh[0], (int32_t)sh[1]));
+    if (pass == Pass::kSuffix)
+      row = std::max(row, rp::gemm_partial_floats(1, (int32_t)sh[0], suffix_splitk(c, (int)sh[0], (int)sh[2], 8)));
+  }
+  if (pass == Pass::kSuffix && half_dtype(c)) {
+    // The attention's partials use the same memory, between the q/k/v and the O projection: as
+    // many chunks as take no more of it than eight K splits would (7B and 32B heads: seven).
+    // Chunks without memory for their partials would all fall to one workgroup: 48 queries
+    // over 16384 keys of a model with one K split, 6 heads of 128, run 315 us in the 4 chunks that
+    // the length asks for and 803 so.
+    const int64_t fit = ((int64_t)row / c.n_q_heads - (rp::attn_part_record(1, c.head_dim) - c.head_dim)) / c.head_dim;
+    p.attn_chunks = (int)std::max<int64_t>(1, std::min<int64_t>(fit, rp::kAttnMostChunks));
+    p.part_floats = std::max(p.part_floats, rp::attn_partial_floats(M, c.n_q_heads, c.head_dim, p.attn_chunks));
   }
   return p;
 }
@@ -358,7 +367,7 @@ struct SuffixWS {
   float* logits;     // [R, V] fp32 (unfused scoring)
   float* lse;        // [R, n_part] float2 and
   float* tgt;        // [R] (fused scoring: RP_SUFFIX_FUSED_LOGPROB)
-  float* gemm_part;
+  float* gemm_part;  // split-K partials and, while they are free, the attention's
   LayerPlan plan;
 };
 
@@ -367,7 +376,7 @@ bool fused_scoring(const rp_model* m, uint32_t flags) {
   return (flags & RP_SUFFIX_FUSED_LOGPROB) && half_dtype(m->cfg);
 }
 
-// Split-KV ways of the suffix attention over prefixes 0 .. n_prefix-1 (the most split).
+// Key chunks that the lengths of prefixes 0 .. n_prefix-1 ask for (the most).
 int32_t suffix_attn_splits(const rp_model* m, int32_t n_prefix, const int32_t* pcu) {
   if (!half_dtype(m->cfg)) return 1;
   int32_t S = 1;
@@ -380,10 +389,9 @@ size_t suffix_ws(const rp_model* m, int64_t R, uint32_t flags, int32_t splits, v
   SuffixWS tmp;
   SuffixWS* s = w ? w : &tmp;
   s->plan = plan_layer(m->cfg, (int32_t)R, Pass::kSuffix);
+  s->plan.part_floats = std::max(s->plan.part_floats,
+                                 rp::attn_partial_floats(R, m->cfg.n_q_heads, m->cfg.head_dim, splits));
   carve_layer(c, m->cfg, R, true, !s->plan.fused, &s->L);
-  const size_t np = rp::attn_partial_floats(R, m->cfg.n_q_heads, m->cfg.head_dim, splits);
-  s->L.attn_part = np ? (float*)c.take(np * 4) : nullptr;
-  s->L.attn_part_floats = (int64_t)np;
   const int64_t kvrow = (int64_t)m->cfg.n_kv_heads * m->cfg.head_dim;
   s->Ks = c.take(R * kvrow * elem_size(m->cfg));
   s->Vs = c.take(R * kvrow * elem_size(m->cfg));
@@ -638,10 +646,9 @@ rp_status run_layer(const rp_model* m, hipStream_t s, const rp_layer_weights& lw
   a.D = D;
   a.scale = (float)(1.0 / sqrt((double)D));
   a.long_keys = gemm_part != nullptr;  // the suffix pass
-  // (the GEMM partials are free between the q/k/v and the o projection)
-  const bool gp = (int64_t)plan.part_floats > w.attn_part_floats;
-  a.part = gp ? gemm_part : w.attn_part;
-  a.part_floats = gp ? (int64_t)plan.part_floats : w.attn_part_floats;
+  a.most_chunks = plan.attn_chunks;
+  a.part = gemm_part;  // (free between the q/k/v and the o projection)
+  a.part_floats = (int64_t)plan.part_floats;
   RP_TRY_LAUNCH_N(nm.attn, rp::launch_attention(s, dt, st, a, M));
   const rp::BSeg bo = wo_operand(c, lw);
   if (s_o > 1) {
@@ -727,6 +734,7 @@ rp_status run_last_rows(const rp_model* m, hipStream_t s, const rp_layer_weights
   a.D = D;
   a.scale = (float)(1.0 / sqrt((double)D));
   a.long_keys = true;
+  a.most_chunks = rp::kAttnMostChunks;
   a.part = t.part;  // (free between the q and the o projection)
   a.part_floats = (int64_t)t.plan.part_floats;
   RP_TRY_LAUNCH_N("prefix.tail_attention", rp::launch_attention(s, dt, tl, a, B));
@@ -1328,6 +1336,29 @@ rp_status rp_calibrate_read(void* stream, const void* src, int64_t bytes, int32_
   const hipError_t e = rp::launch_read_probe((hipStream_t)stream, src, bytes, blocks, sink);
   if (e != hipSuccess) return fail(RP_ERR_HIP, "read probe launch: %s", hipGetErrorString(e));
   return RP_OK;
+}
+
+// ---- for the tests: the form a launch would take (nothing is launched; not in rollplex.h) ----
+
+// Key-chunk attention of a suffix pass with its own workspace: chunk slots S of the launch, -S
+// where a workgroup takes all S chunks of a sequence.
+int32_t rp_test_suffix_chunks(const rp_model* m, int32_t n_prefix, const int32_t* pcu, int32_t n_suffix,
+                              const int32_t* prefix_of_suffix, const int32_t* scu) {
+  if (!m || check_grouped_cu(m, n_prefix, pcu, n_suffix, prefix_of_suffix, scu) != RP_OK || !half_dtype(m->cfg)) return 0;
+  SuffixWS w;
+  suffix_ws(m, scu[n_suffix], 0u, suffix_attn_splits(m, n_prefix, pcu), nullptr, &w);
+  const rp::SeqTable tab = make_table(n_suffix, scu, n_prefix, pcu, prefix_of_suffix);
+  float there = 0.f;
+  rp::AttnArgs a{};
+  a.Hq = m->cfg.n_q_heads;
+  a.Hkv = m->cfg.n_kv_heads;
+  a.D = m->cfg.head_dim;
+  a.long_keys = true;
+  a.most_chunks = w.plan.attn_chunks;
+  a.part = &there;  // stands for the workspace's memory
+  a.part_floats = (int64_t)w.plan.part_floats;
+  const rp::AttnLongPlan p = rp::attn_long_plan(tab, a, scu[n_suffix]);
+  return p.fold ? -p.chunks : p.S;
 }
 
 int rp_device_cu_count(int device) {

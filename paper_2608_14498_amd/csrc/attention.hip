@@ -206,7 +206,7 @@ void k_attn_bf16(SeqTable st, AttnArgs a) {
   // chunk also the segment-1 tiles (the causal keys): it is the longest and runs at
   // blockIdx.y 0.
   int t_begin = 0, t_end = P0 + (qpos_last - n0 + KT) / KT, chunk = 0;
-  const int nch = LONG ? attn_chunks(n0, nq, a.Hq, a.Hkv) : 1;
+  const int nch = LONG ? attn_chunks(n0, nq, a.Hq, a.Hkv, a.most_chunks) : 1;
   const bool split = FORM == kLong && nch > 1;
   if (FORM == kLong && (int)blockIdx.y >= nch) return;
   auto chunk_end = [&](int c) { return c + 1 < nch ? P0 * (c + 1) / nch : t_end; };
@@ -682,14 +682,14 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(SeqTable st, AttnArgs a) {
 // when it takes them all.
 template <typename T16, int D>
 __global__ __launch_bounds__(256) void k_attn_split_merge(SeqTable st, const float* __restrict__ part, int S, int Hq,
-                                                          int Hkv, int64_t items, T16* __restrict__ o) {
+                                                          int Hkv, int most, int64_t items, T16* __restrict__ o) {
   typedef Half16<T16> H;
   constexpr int PER = D / 64;
   const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (item >= items) return;
   const int lane = threadIdx.x & 63;
   const int b = seq_of_row(st, (int)(item / Hq));
-  const int nch = attn_chunks(st.pos0(b), st.q_cu[b + 1] - st.q_cu[b], Hq, Hkv);
+  const int nch = attn_chunks(st.pos0(b), st.q_cu[b + 1] - st.q_cu[b], Hq, Hkv, most);
   if (nch == 1) return;
   const float* p = part + item * attn_part_record(S, D);
   const float* ml = p + S * D;
@@ -736,6 +736,30 @@ int count_qblocks(const SeqTable& st, int BQ, int P = 1) {
   return n;
 }
 
+// Long sequences: 8 waves (256 rows) share each K/V tile, halving the tile loads per query;
+// shorter ones keep 4 waves, whose smaller blocks balance better.  Each wave sees the same rows
+// and key tiles in the same order either way (same results).
+static bool attn_wide(const SeqTable& st) {
+  int max_q = 0;
+  for (int b = 0; b < st.n; ++b) max_q = std::max(max_q, st.q_cu[b + 1] - st.q_cu[b]);
+  return max_q >= 8192;
+}
+
+// The chunks go to workgroups of their own while the blocks alone leave CUs short of the two
+// workgroups that they hold and the partials fit the scratch memory at hand.
+AttnLongPlan attn_long_plan(const SeqTable& st, const AttnArgs& a, int32_t total_q) {
+  AttnLongPlan p;
+  p.wide = attn_wide(st);
+  p.grid = fa_grid(fa_map(a.Hkv, a.Hkv), count_qblocks(st, p.wide ? 256 : 128, a.Hq / a.Hkv), a.Hkv);
+  p.chunks = 1;
+  for (int b = 0; b < st.n; ++b)
+    p.chunks = std::max(p.chunks, attn_chunks(st.pos0(b), st.q_cu[b + 1] - st.q_cu[b], a.Hq, a.Hkv, a.most_chunks));
+  const bool fit = a.part && (int64_t)attn_partial_floats(total_q, a.Hq, a.D, p.chunks) <= a.part_floats;
+  p.fold = p.chunks > 1 && (p.grid >= 512 || !fit);
+  p.S = p.fold ? 1 : p.chunks;
+  return p;
+}
+
 // Timing-harness hook: forced tile shape (0: 32 queries/wave x 64-key tiles,
 // 1: 64 queries/wave x 32-key tiles).
 hipError_t launch_attention_variant(hipStream_t s, int variant, const SeqTable& st, const AttnArgs& a) {
@@ -758,25 +782,11 @@ hipError_t launch_attention(hipStream_t s, rp_dtype dt, const SeqTable& st, cons
     hipError_t e = hipSuccess;
     with_half16(dt, [&](auto tag_) {
       using H = decltype(tag_);
-      // Long sequences: 8 waves (256 rows) share each K/V tile, halving the tile loads
-      // per query; shorter ones keep 4 waves, whose smaller blocks balance better.  Each
-      // wave sees the same rows and key tiles in the same order either way (same results).
-      int max_q = 0;
-      for (int b = 0; b < st.n; ++b) max_q = std::max(max_q, st.q_cu[b + 1] - st.q_cu[b]);
-      const bool wide = max_q >= 8192;
-      const int BQ = wide ? 256 : 128;
       if (a.long_keys) {
-        const int P = a.Hq / a.Hkv;
-        const int grid = fa_grid(fa_map(a.Hkv, a.Hkv), count_qblocks(st, BQ, P), a.Hkv);
-        // The chunks go to workgroups of their own while the blocks alone leave CUs short of
-        // the two workgroups that they hold and the partials fit the scratch memory at hand.
-        int chunks = 1;
-        for (int b = 0; b < st.n; ++b)
-          chunks = std::max(chunks, attn_chunks(st.pos0(b), st.q_cu[b + 1] - st.q_cu[b], a.Hq, a.Hkv));
-        const bool fit = a.part && (int64_t)attn_partial_floats(total_q, a.Hq, a.D, chunks) <= a.part_floats;
-        const bool fold = chunks > 1 && (grid >= 512 || !fit);
-        const int S = fold ? 1 : chunks;
-        const dim3 g(grid, S);
+        const AttnLongPlan lp = attn_long_plan(st, a, total_q);
+        const bool wide = lp.wide, fold = lp.fold;
+        const int S = lp.S;
+        const dim3 g(lp.grid, S);
         auto run = [&](auto d_, auto nw_) {
           constexpr int D = decltype(d_)::value, NW = decltype(nw_)::value;
           if (fold)
@@ -797,13 +807,14 @@ hipError_t launch_attention(hipStream_t s, rp_dtype dt, const SeqTable& st, cons
           const int64_t items = (int64_t)total_q * a.Hq;
           const int mgrid = (int)((items + 3) / 4);
           if (a.D == 128)
-            k_attn_split_merge<H, 128><<<mgrid, 256, 0, s>>>(st, a.part, S, a.Hq, a.Hkv, items, (H*)a.o);
+            k_attn_split_merge<H, 128><<<mgrid, 256, 0, s>>>(st, a.part, S, a.Hq, a.Hkv, a.most_chunks, items, (H*)a.o);
           else
-            k_attn_split_merge<H, 64><<<mgrid, 256, 0, s>>>(st, a.part, S, a.Hq, a.Hkv, items, (H*)a.o);
+            k_attn_split_merge<H, 64><<<mgrid, 256, 0, s>>>(st, a.part, S, a.Hq, a.Hkv, a.most_chunks, items, (H*)a.o);
         }
         return;
       }
-      const int grid = fa_grid(fa_map(a.Hq, a.Hkv), count_qblocks(st, BQ), a.Hq);
+      const bool wide = attn_wide(st);
+      const int grid = fa_grid(fa_map(a.Hq, a.Hkv), count_qblocks(st, wide ? 256 : 128), a.Hq);
       if (a.D == 128) {
         if (wide)
           k_attn_bf16<H, 128, 1, 64, 8, kDense><<<grid, 512, 0, s>>>(st, a);

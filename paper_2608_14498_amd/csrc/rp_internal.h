@@ -198,16 +198,18 @@ struct AttnArgs {
   float scale;
   // 16-bit models, queries over a long first key segment (suffix pass, last rows of a prefix):
   // pack the q heads of a kv head into the query blocks and cut a sequence's keys into
-  // attn_chunks() chunks.  part (part_floats floats of scratch, may be null) lets a launch of
-  // few blocks give each chunk a workgroup: one record of attn_part_record(S, D) floats per
-  // (query row, head) for S chunk slots, chunk c's unnormalised o at c * D and its (max, sum)
-  // at S * D + 2 c, so each chunk's o is whole 128-byte lines written by one workgroup.
+  // attn_chunks() chunks, most_chunks at most.  part (part_floats floats of scratch, may be null)
+  // lets a launch of few blocks give each chunk a workgroup: one record of
+  // attn_part_record(S, D) floats per (query row, head) for S chunk slots, chunk c's
+  // unnormalised o at c * D and its (max, sum) at S * D + 2 c, so each chunk's o is whole
+  // 128-byte lines written by one workgroup.
   bool long_keys = false;
+  int most_chunks = 1;
   float* part = nullptr;
   int64_t part_floats = 0;
 };
 __host__ __device__ inline int attn_part_record(int S, int D) { return S * D + 32; }
-// Scratch set aside for chunk partials: this many ways for a first segment of n0 keys.
+// Chunks of a first segment of n0 keys whatever the queries.
 #ifndef RP_ATTN_SPLIT_KEYS
 #define RP_ATTN_SPLIT_KEYS 4096
 #endif
@@ -217,21 +219,28 @@ __host__ __device__ inline int attn_splits(int n0) {
   return sp < 1 ? 1 : (sp > kAttnMaxSplits ? kAttnMaxSplits : sp);
 }
 // Key chunks of a sequence of nq queries over n0 first-segment keys: a function of the sequence
-// and the head counts alone, so its result does not depend on the sequences packed with it.
-// As many as bring the sequence to about 64 workgroups, of 256 keys or more: 48 queries over
-// 1501 keys (7B heads) run 36 -> 23 us a layer.  Aiming at 128 cut 4 responses of 256 tokens in
-// two and left them at 100 us (two workgroups on a CU each run at little over half speed).
-// Long segments are cut whatever the queries.  At most 7, since partials of 7 chunks fit the
-// memory of a down projection's partials.
-__host__ __device__ inline int attn_chunks(int n0, int nq, int Hq, int Hkv) {
+// and the model (head counts, most) alone, so its result does not depend on the sequences packed
+// with it.  As many as bring the sequence to about 64 workgroups, of 256 keys or more: 48 queries
+// over 1501 keys (7B heads) run 36 -> 23 us a layer.  Aiming at 128 cut 4 responses of 256 tokens
+// in two and left them at 100 us (two workgroups on a CU each run at little over half speed).
+// At most `most` (up to kAttnMostChunks), but long segments are cut whatever the queries.
+constexpr int kAttnMostChunks = 7;
+__host__ __device__ inline int attn_chunks(int n0, int nq, int Hq, int Hkv, int most) {
   if (nq <= 0) return 1;  // an empty response
   const int blocks = (nq * (Hq / Hkv) + 127) / 128 * Hkv;
   int c = (64 + blocks / 2) / blocks;
   c = c < n0 / 256 ? c : n0 / 256;
-  c = c < 7 ? c : 7;
+  c = c < most ? c : most;
   const int least = attn_splits(n0);
   return c > least ? c : least;
 }
+// How a long_keys launch runs: `wide` blocks of 256 rows (else 128) in `grid` workgroups a chunk
+// slot, each taking one chunk (S slots, then merged) or, where `fold`, all of them.
+struct AttnLongPlan {
+  bool wide, fold;
+  int grid, chunks, S;
+};
+AttnLongPlan attn_long_plan(const SeqTable& st, const AttnArgs& a, int32_t total_q);
 // Partial floats for R query rows whose sequences split at most max_splits ways.
 size_t attn_partial_floats(int64_t R, int32_t Hq, int32_t D, int32_t max_splits);
 hipError_t launch_attention(hipStream_t s, rp_dtype dt, const SeqTable& st, const AttnArgs& a,

@@ -1,0 +1,55 @@
+"""Which kernels a call's launches take, asked of the library without a GPU: the rules of the
+dispatch have to hold over the shapes of all models, not only at the sizes they were timed at."""
+import ctypes
+from dataclasses import replace
+
+import pytest
+
+from paper_2608_14498_amd import binding as rb
+from paper_2608_14498_amd import configs
+from tests.test_abi_cpu import make
+
+SMALL = configs.ModelShape(n_layers=2, d_model=512, n_q_heads=6, n_kv_heads=3, head_dim=128, ffn_dim=1536, vocab=4096,
+                           dtype="bf16")
+SMALL64 = replace(SMALL, n_q_heads=8, n_kv_heads=2, head_dim=64, ffn_dim=1024, dtype="f16")
+TWO_WAYS = replace(SMALL, ffn_dim=2048)  # a down projection in two K splits
+
+
+def suffix_chunks(handle, prefix, lens):
+    """Key-chunk slots of the suffix attention of responses `lens` over one prefix (negative: a
+    workgroup takes all chunks)."""
+    arr = lambda v: (ctypes.c_int32 * len(v))(*v)
+    f = rb.lib().rp_test_suffix_chunks
+    f.restype = ctypes.c_int32
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    return f(handle, 1, arr([0, prefix]), len(lens), arr([0] * len(lens)), arr(cu))
+
+
+@pytest.mark.parametrize("model", [SMALL, SMALL64, TWO_WAYS, configs.QWEN7B_SLICE, configs.QWEN32B_SLICE])
+def test_a_lone_response_spreads_a_long_prefix_over_workgroups(model):
+    """At least the chunks that the prefix's length asks for (one per 4096 keys, eight at most),
+    each on a workgroup of its own: the workspace holds their partials for every model."""
+    h, keep = make(model, 60000)
+    try:
+        for prefix in (300, 4096, 8191, 8192, 12288, 16384, 30000, 32768, 50000):
+            for n in (1, 48, 64, 300, 900):
+                got = suffix_chunks(h, prefix, [n])
+                assert got >= max(1, min(8, prefix // 4096)), (prefix, n, got)
+    finally:
+        rb.rp_destroy(h)
+
+
+@pytest.mark.parametrize("model", [configs.QWEN7B_SLICE, configs.QWEN32B_SLICE])
+def test_suffix_partials_share_one_memory(model):
+    """The attention's partials lie in the GEMMs' memory: up to seven chunks a longer prefix asks
+    for no more workspace (R responses' tokens and the logits alone count)."""
+    h, keep = make(model, 60000)
+    try:
+        want = {p: rb.rp_suffix_workspace_bytes(h, 1, [0, p], [0, 256]) for p in (300, 4096, 8192, 16384, 30000)}
+        assert len(set(want.values())) == 1, want
+        assert rb.rp_suffix_workspace_bytes(h, 1, [0, 40000], [0, 256]) >= want[300]
+    finally:
+        rb.rp_destroy(h)
