@@ -1340,6 +1340,12 @@ rp_status rp_calibrate_read(void* stream, const void* src, int64_t bytes, int32_
 
 // ---- for the tests: the form a launch would take (nothing is launched; not in rollplex.h) ----
 
+// Form (rp::GemmForm) and flexible tile of a GEMM.
+int32_t rp_test_gemm_form(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t trans, int32_t epi, int32_t splitk,
+                          int32_t* tile) {
+  return rp::gemm_form((rp_dtype)dtype, M, N, K, trans != 0, (rp::Epi)epi, splitk, tile);
+}
+
 // Key-chunk attention of a suffix pass with its own workspace: chunk slots S of the launch, -S
 // where a workgroup takes all S chunks of a sequence.
 int32_t rp_test_suffix_chunks(const rp_model* m, int32_t n_prefix, const int32_t* pcu, int32_t n_suffix,

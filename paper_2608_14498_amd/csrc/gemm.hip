@@ -1105,10 +1105,16 @@ int32_t gemm_effective_splitk(rp_dtype dt, int32_t K, int32_t splitk) {
 // us, whole / cut: 7B down projection of 14229 rows (784 tiles, 3.06 rounds) 1800 / 1539,
 // gate/up of 1024 rows (592, 2.3) 258 / 241, lm_head of 1024 rows (2376, 9.3) 1017 / 992;
 // 32B down projection of 10000 rows 2600 / 2210.
+// A tail of rows reads all of B a second time.  Where B is far more than the Infinity Cache's
+// 256 MB and that read is all of the tail's cost, it takes 7% more than at 5 TB/s (lm_head of 130
+// rows: 234 us for 218): else the fused lm_head of 880 and 926 rows was cut after 768, 977 and 1004
+// us a call, cut by columns 926 and 926 (whole: 942 and 950).  A gate/up projection of 271 MB is
+// cut by rows: two layers of 2570 rows 2437 us a call, by columns 2493.
 static bool cut_last_round(GemmArgs* g, GemmArgs* tail, int epi, int c_bytes) {
   const int nt = epi == EPI_SWIGLU ? 128 : GB_N;  // output columns of a tile
   const int64_t tm = (g->M + GB_M - 1) / GB_M, tn = (g->N + nt - 1) / nt;
   const int64_t full = tm * tn / 256 * 256;
+  const bool big_b = 2. * g->K * g->N * (epi == EPI_SWIGLU ? 2. : 1.) > 512e6;
   double best = gemm_cost_256(*g, epi, 1) * 0.97;  // below 3% the second launch is not worth it
   GemmArgs head_best, tail_best;
   bool found = false;
@@ -1140,7 +1146,8 @@ static bool cut_last_round(GemmArgs* g, GemmArgs* tail, int epi, int c_bytes) {
       t.n_off = (int)n;
       if (epi != EPI_LSE && epi != EPI_ROPE) t.C = (char*)g->C + n * c_bytes;
     }
-    const double cost = gemm_cost_256(h, epi, 1) + gemm_cost_flex(t, epi, 1) + 3000.;
+    const double cost_tail = std::max(gemm_cost_flex(t, epi, 1), rows && big_b ? 1.07 * gemm_hbm_floor(t, epi, 1) : 0.);
+    const double cost = gemm_cost_256(h, epi, 1) + cost_tail + 3000.;
     if (cost < best) {
       best = cost;
       head_best = h;
@@ -1160,6 +1167,76 @@ static bool cut_last_round(GemmArgs* g, GemmArgs* tail, int epi, int c_bytes) {
 bool gemm_swiglu_chunks(rp_dtype dt, int32_t M, int32_t N, int32_t K, int32_t splitk) {
   return dt != RP_F32 && M <= 64 && K % GB_K == 0 && gemm_effective_splitk(dt, K, splitk) <= 3 &&
          (uint64_t)N * K * 2u <= 0xFFFFFF00ull;
+}
+
+// The kernels of one GEMM: g (and tail, the launch that follows where the last round is cut).
+struct GemmChoice {
+  GemmForm form;
+  GemmArgs g, tail;
+  int splitk;
+  bool split;      // partials (summed by the caller, or by the reduction)
+  int epi;         // epilogue of the kernel (-1: partials)
+  int64_t b_rows;  // logical rows of B
+};
+static GemmChoice gemm_choose(rp_dtype dt, Epi epi, int splitk, GemmArgs g) {
+  const bool half = dt != RP_F32;
+  GemmChoice c;
+  if (splitk < 1) splitk = 1;
+  const int bk = half ? GB_K : GF_K;
+  const int kblocks = (g.K + bk - 1) / bk;
+  if (splitk > kblocks) splitk = kblocks;
+  g.k_chunk = ((kblocks + splitk - 1) / splitk) * bk;
+  splitk = (g.K + g.k_chunk - 1) / g.k_chunk;
+  if (epi == EPI_SWIGLU && splitk > 1) {  // the chunks are summed in the kernel
+    g.k_sum = g.k_chunk;
+    g.k_chunk = g.K;
+    splitk = 1;
+  }
+  c.splitk = splitk;
+  // EPI_PARTIALS: the partials epilogue even for one split, and no reduction here
+  c.split = splitk > 1 || epi == EPI_PARTIALS;
+  c.b_rows = epi == EPI_SWIGLU ? (int64_t)g.B.n1 + g.N : g.N;
+  c.epi = c.split ? -1 : (int)epi;
+  c.g = g;
+  c.form = kGemmF32;
+  if (!half) return c;
+  const bool flex_ok = (epi != EPI_STORE || c.split) && dma_setup(g, c.b_rows, epi == EPI_SWIGLU);
+  if (g.k_sum) {
+    c.form = flex_ok ? kGemmFlex : kGemmNone;
+    return c;
+  }
+  const bool flex = flex_ok && gemm_cost_flex(g, c.epi, splitk) < 0.9 * gemm_cost_256(g, c.epi, splitk);
+  // Up to 64 rows the skinny kernel streams the weights with three workgroups of two stages
+  // per CU; where its launch is less than one such workgroup per CU, the flexible tile's deeper
+  // ring reads faster (same bits).  Of 48 rows, 7B shapes, us (with timing events), skinny /
+  // flexible: q/k/v in 3 splits (108 workgroups) 21 / 16, down in 8 (224) 44 / 36; a decode
+  // step's 504 and 448 workgroups: 15 / 19 and 36 / 38.
+  if (skinny_setup(g, epi, c.split) && !(flex && (int64_t)((g.N + 127) / 128) * splitk <= 256)) {
+    c.form = kGemmSkinny;
+  } else if (flex) {
+    c.form = kGemmFlex;
+  } else {
+    const bool cut = flex_ok && !c.split && cut_last_round(&c.g, &c.tail, epi, epi == EPI_SWIGLU ? 2 : 4);
+    c.form = !cut ? kGemm256 : c.tail.M < g.M ? kGemmCutRows : kGemmCutCols;
+  }
+  return c;
+}
+
+GemmForm gemm_form(rp_dtype dt, int32_t M, int32_t N, int32_t K, bool trans, Epi epi, int32_t splitk, int32_t* tile) {
+  GemmArgs g{};
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.lda = K;
+  g.B = BSeg{nullptr, nullptr, nullptr, N, epi == EPI_SWIGLU ? 2 * N : N, trans};
+  g.ldb = trans ? N : K;
+  g.ldc = N;
+  g.n_part = lse_parts(N);
+  g.n_all = N;
+  const GemmChoice c = gemm_choose(dt, epi, splitk, g);
+  *tile = c.form == kGemmFlex ? gemm_flex_tile(c.g, c.epi, c.splitk)
+          : c.form == kGemmCutRows || c.form == kGemmCutCols ? gemm_flex_tile(c.tail, c.epi, 1) : 0;
+  return c.form;
 }
 
 hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t K, const void* A,
@@ -1194,31 +1271,12 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
   g.rope = rope ? *rope : RopeOut{};
   g.n_part = lse_parts(N);
   g.n_all = N;
-  if (splitk < 1) splitk = 1;
-  const int bk = half ? GB_K : GF_K;
-  const int kblocks = (K + bk - 1) / bk;
-  if (splitk > kblocks) splitk = kblocks;
-  g.k_chunk = ((kblocks + splitk - 1) / splitk) * bk;
-  splitk = (K + g.k_chunk - 1) / g.k_chunk;
-  if (epi == EPI_SWIGLU && splitk > 1) {  // the chunks are summed in the kernel
-    g.k_sum = g.k_chunk;
-    g.k_chunk = K;
-    splitk = 1;
-  }
-  // EPI_PARTIALS: the partials epilogue even for one split, and no reduction here
-  const bool split = splitk > 1 || epi == EPI_PARTIALS;
-  const int64_t b_rows = epi == EPI_SWIGLU ? (int64_t)B.n1 + N : N;
-  const int fepi = split ? -1 : (int)epi;
-  const bool flex_ok = half && (epi != EPI_STORE || split) && dma_setup(g, b_rows, epi == EPI_SWIGLU);
-  if (g.k_sum && !flex_ok) return hipErrorInvalidValue;
-  const double cost_256 = g.k_sum ? 1e30 : gemm_cost_256(g, fepi, splitk);
-  const bool flex = flex_ok && gemm_cost_flex(g, fepi, splitk) < 0.9 * cost_256;
-  // Up to 64 rows the skinny kernel streams the weights with three workgroups of two stages
-  // per CU; where its launch is less than one such workgroup per CU, the flexible tile's deeper
-  // ring reads faster (same bits).  Of 48 rows, 7B shapes, us (with timing events), skinny /
-  // flexible: q/k/v in 3 splits (108 workgroups) 21 / 16, down in 8 (224) 44 / 36; a decode
-  // step's 504 and 448 workgroups: 15 / 19 and 36 / 38.
-  if (half && skinny_setup(g, epi, split) && !(flex && (int64_t)((N + 127) / 128) * splitk <= 256)) {
+  GemmChoice c = gemm_choose(dt, epi, splitk, g);
+  if (c.form == kGemmNone) return hipErrorInvalidValue;
+  g = c.g;
+  splitk = c.splitk;
+  const bool split = c.split;
+  if (c.form == kGemmSkinny) {
     // split: partials (summed by the caller, or by the reduction below); else C itself
     with_half16(dt, [&](auto tag_) {
       using H = decltype(tag_);
@@ -1227,12 +1285,11 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
       else
         launch_skinny<H>(s, g, 1, (float*)C, ldc, 0, epi == EPI_ADD_F32);
     });
-  } else if (flex) {
-    const hipError_t em = launch_flex_gemm(s, dt, fepi, g, splitk);
+  } else if (c.form == kGemmFlex) {
+    const hipError_t em = launch_flex_gemm(s, dt, c.epi, g, splitk);
     if (em != hipSuccess) return em;
   } else if (half) {
-    GemmArgs tail;
-    const bool cut = flex_ok && !split && cut_last_round(&g, &tail, epi, epi == EPI_SWIGLU ? 2 : 4);
+    const int64_t b_rows = c.b_rows;
     g.tiles_m = (g.M + GB_M - 1) / GB_M;
     g.tiles_n = epi == EPI_SWIGLU ? (g.N + 127) / 128 : (g.N + GB_N - 1) / GB_N;
     dim3 grid(g.tiles_m * g.tiles_n, splitk);
@@ -1257,8 +1314,8 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
       else
         launch_half<EPI_ADD_F32, H>(s, g, grid, b_rows);
     });
-    if (cut) {
-      const hipError_t em = launch_flex_gemm(s, dt, epi, tail, 1);
+    if (c.form != kGemm256) {
+      const hipError_t em = launch_flex_gemm(s, dt, epi, c.tail, 1);
       if (em != hipSuccess) return em;
     }
   } else {

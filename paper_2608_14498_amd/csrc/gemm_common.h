@@ -238,7 +238,10 @@ __device__ __forceinline__ void store_rows(const GemmArgs& g, const F32Out& out,
 }
 
 // GEMM over small tiles (gemm_flex.hip): the cost in ns of the best tile (and of the
-// 256x256 kernel), by which the dispatch picks.
+// 256x256 kernel), by which the dispatch picks; the time that HBM takes for B and the output; the
+// best tile as 100 RF + 10 SW + NS.
+double gemm_hbm_floor(const GemmArgs& g, int epi, int splitk);
+int gemm_flex_tile(const GemmArgs& g, int epi, int splitk);
 double gemm_cost_256(const GemmArgs& g, int epi, int splitk);
 double gemm_cost_flex(const GemmArgs& g, int epi, int splitk);
 hipError_t launch_flex_gemm(hipStream_t s, rp_dtype dt, int epi, const GemmArgs& g, int splitk);

@@ -371,7 +371,7 @@ static int flex_cols(const GemmArgs& g, int epi, int SW) {
 }
 
 // Time in ns that HBM takes for B and the output, which no tile avoids.
-static double hbm_floor(const GemmArgs& g, int epi, int splitk) {
+double gemm_hbm_floor(const GemmArgs& g, int epi, int splitk) {
   const double out = (double)g.M * g.N;
   const double bytes = 2. * g.K * g.N * (epi == EPI_SWIGLU ? 2. : 1.) +
                        (epi == -1 ? 5. * splitk * out : epi == EPI_SWIGLU || epi == EPI_ROPE ? 2. * out : epi == EPI_LSE ? 0. : 4. * out);
@@ -382,11 +382,11 @@ double gemm_cost_256(const GemmArgs& g, int epi, int splitk) {
   const int64_t tiles = (int64_t)((g.M + 255) / 256) * (epi == EPI_SWIGLU ? (g.N + 127) / 128 : (g.N + 255) / 256) * splitk;
   const double kt = g.k_chunk / GB_K, full = (double)(tiles / 256), rem = (double)(tiles % 256);
   const double t = full * (kt * 1426. + 12000.) + (rem > 0 ? kt * (1170. + rem) + 12000. : 0.);
-  return std::max(t, hbm_floor(g, epi, splitk));
+  return std::max(t, gemm_hbm_floor(g, epi, splitk));
 }
 
 static int flex_pick(const GemmArgs& g, int epi, int splitk, double* best) {
-  const double kt = g.k_chunk / GB_K, floor = hbm_floor(g, epi, splitk);
+  const double kt = g.k_chunk / GB_K, floor = gemm_hbm_floor(g, epi, splitk);
   int pick = 0;
   double least = 1e30;
   for (int i = 0; i < (int)(sizeof kFlexTiles / sizeof kFlexTiles[0]); ++i) {
@@ -457,6 +457,12 @@ static void launch_flex_t(hipStream_t s, int epi, GemmArgs g, int splitk) {
     else
       k_gemm_flex<EPI_ADD_F32, T16, RF, SW, NS><<<grid, SW * 64, 0, s>>>(g);
   }
+}
+
+int gemm_flex_tile(const GemmArgs& g, int epi, int splitk) {
+  double cost;
+  const FlexTile& f = kFlexTiles[flex_pick(g, epi, splitk, &cost)];
+  return 100 * f.RF + 10 * f.SW + f.NS;
 }
 
 hipError_t launch_flex_gemm(hipStream_t s, rp_dtype dt, int epi, const GemmArgs& g, int splitk) {

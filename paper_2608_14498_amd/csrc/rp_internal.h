@@ -158,6 +158,10 @@ hipError_t launch_gemm(hipStream_t s, rp_dtype dt, int32_t M, int32_t N, int32_t
                        int32_t lda, const BSeg& B, int32_t ldb, void* C, int32_t ldc, Epi epi,
                        int32_t splitk, float* partials, const LseOut* lse = nullptr,
                        const RopeOut* rope = nullptr);
+// The kernel that a GEMM of these sizes takes (contiguous operands), and its flexible tile, if
+// any, as 100 RF + 10 SW + NS (the tail's where the last round is cut).
+enum GemmForm { kGemmNone, kGemmF32, kGemmSkinny, kGemmFlex, kGemm256, kGemmCutRows, kGemmCutCols };
+GemmForm gemm_form(rp_dtype dt, int32_t M, int32_t N, int32_t K, bool trans, Epi epi, int32_t splitk, int32_t* tile);
 bool gemm_swiglu_chunks(rp_dtype dt, int32_t M, int32_t N, int32_t K, int32_t splitk);
 // out[m] = argmax over n of (A . B^T)[m][n] (lowest n among equal maxima; NaN never wins; -1
 // when a row has no candidate); C (fp32 [M][N]) is stored unless NULL.  16-bit, one B segment [N][K], M <= 64,
