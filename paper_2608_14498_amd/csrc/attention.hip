@@ -857,6 +857,32 @@ hipError_t launch_attention(hipStream_t s, rp_dtype dt, const SeqTable& st, cons
 constexpr int DC_KEYS = 1024;  // keys per chunk (one wave)
 constexpr int DC_MAXG = 8;    // q heads per kv head (validated on the host)
 
+// Output of a decode attention: PER head dimensions of o, times 1 / l, stored as T.  The forms
+// that a batch size picks give one sequence the same bits, so the conversion is fixed here and
+// not the compiler's choice: one dimension a lane (D = 64) in fp16 is a product and conversion
+// with a single rounding, pairs are rounded to fp32 first.
+template <typename T>
+__device__ __forceinline__ uint32_t scaled16(float x, float s) {
+  if constexpr (std::is_same<T, f16_t>::value) {
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(r) : "v"(x), "v"(s));
+    return r & 0xffffu;
+  } else {
+    return (uint32_t)f2bf(x * s);
+  }
+}
+template <typename T, int PER>
+__device__ __forceinline__ void store_scaled(T* p, const float (&o)[PER], float s) {
+  if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) p[e] = o[e] * s;
+  } else if constexpr (PER == 1) {
+    *reinterpret_cast<uint16_t*>(p) = (uint16_t)scaled16<T>(o[0], s);
+  } else {
+    *reinterpret_cast<uint32_t*>(p) = Half16<T>::pack2(o[0] * s, o[1] * s);
+  }
+}
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_decode_attn_part(const T* __restrict__ q, int q_ld,
                                                           const T* __restrict__ ck, const T* __restrict__ cv,
@@ -1303,9 +1329,18 @@ __global__ __launch_bounds__(64 * (DEEP ? 1 : DC_WAVES)) void k_decode_attn_mfma
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
-          const float v[4] = {o[db][4 * e4] * inv, o[db][4 * e4 + 1] * inv, o[db][4 * e4 + 2] * inv,
-                              o[db][4 * e4 + 3] * inv};
-          store4(oh + db * 32 + 8 * e4 + 4 * fk, v);
+          float v[4];  // (+ 0: the merge adds its one record to 0)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] = o[db][4 * e4 + t] + 0.f;
+          uint2 w;
+          if constexpr (D == 64) {
+            w.x = scaled16<T16>(v[0], inv) | scaled16<T16>(v[1], inv) << 16;
+            w.y = scaled16<T16>(v[2], inv) | scaled16<T16>(v[3], inv) << 16;
+          } else {
+            w.x = H::pack2(v[0] * inv, v[1] * inv);
+            w.y = H::pack2(v[2] * inv, v[3] * inv);
+          }
+          *reinterpret_cast<uint2*>(oh + db * 32 + 8 * e4 + 4 * fk) = w;
         }
     }
     return;
@@ -1387,8 +1422,7 @@ __global__ __launch_bounds__(256) void k_decode_chunk_merge(const float* __restr
     for (int e = 0; e < PER; ++e) acc[e] = fmaf(wr, og[e], acc[e]);
   }
   const float inv = 1.0f / L;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) stf(o + (int64_t)item * D + lane * PER + e, acc[e] * inv);
+  store_scaled(o + (int64_t)item * D + lane * PER, acc, inv);
 }
 
 // Merge of the decode chunks: one wave per (sequence, q head).  Lane c holds chunk c's
@@ -1426,8 +1460,7 @@ __global__ __launch_bounds__(256) void k_decode_attn_merge(const float* __restri
   }
   L = wave_sum(L);
   const float inv = 1.0f / L;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) stf(o + (int64_t)item * D + lane * PER + e, acc[e] * inv);
+  store_scaled(o + (int64_t)item * D + lane * PER, acc, inv);
 }
 
 size_t decode_attn_partial_floats(int32_t B, int32_t Hq, int32_t D, int32_t cap) {

@@ -1,7 +1,8 @@
 """The forms a decode step takes by batch size give one sequence the same bits: alone it runs
 one wave per 1024-key chunk (deep ring, chunk merge), in a large batch three chunks per
-workgroup, with one record (the result written directly) or several.  The gate/up projection
-with its chunked sums (F >= 12800) is compared with the oracle."""
+workgroup, with one record (the result written directly) or several.  Where both forms convert
+to fp16 a single rounding can fall otherwise once in some 2^13 values, so that model's sequences
+are all compared."""
 from dataclasses import replace
 
 import numpy as np
@@ -17,15 +18,16 @@ pytestmark = pytest.mark.gpu
 
 WIDE_F = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=4, head_dim=128, ffn_dim=12800,
                             vocab=1003, dtype="bf16")
-F16_D64 = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=4, head_dim=64, ffn_dim=512,
+F16_D64 = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=16, n_kv_heads=2, head_dim=64, ffn_dim=512,
                              vocab=1003, dtype="f16")
 
 
-@pytest.mark.parametrize("model,cap,edges", [
-    (WIDE_F, 2200, [0, 1, 31, 32, 33, 1023, 1024, 1056, 2047, 2048, 2199]),
-    (replace(WIDE_F, dtype="f16"), 4200, [159, 160, 161, 3071, 3072, 3073, 4199]),
-    (F16_D64, 3000, [0, 127, 1025, 2999])])
-def test_alone_and_in_a_batch_the_same_bits(model, cap, edges):
+@pytest.mark.parametrize("model,cap,edges,alone", [
+    (WIDE_F, 2200, [0, 1, 31, 32, 33, 1023, 1024, 1056, 2047, 2048, 2199], 11),
+    (replace(WIDE_F, dtype="f16"), 4200, [159, 160, 161, 3071, 3072, 3073, 4199], 7),
+    (F16_D64, 3000, [0, 127, 1025, 2999], 63),   # one record
+    (F16_D64, 3100, [0, 127, 1025, 3099], 63)])  # two
+def test_alone_and_in_a_batch_the_same_bits(model, cap, edges, alone):
     B = 63
     w = configs.custom(model, [1], [0], [1], index=86)
     hw = inputs.make_weights(w, norm="random", bias=True)
@@ -44,10 +46,13 @@ def test_alone_and_in_a_batch_the_same_bits(model, cap, edges):
     lg, nx = step(list(range(B)))
     assert torch.isfinite(lg).all()
     assert torch.equal(nx.long(), lg.argmax(1))
-    for b in range(len(edges)):
-        print("alone", int(kv_len[b]), flush=True)
+    print("model", model.dtype, model.head_dim, "cap", cap, flush=True)
+    differ = []
+    for b in range(alone):
         l1, n1 = step([b])
-        assert torch.equal(l1[0], lg[b]) and int(n1[0]) == int(nx[b])
+        if not (torch.equal(l1[0], lg[b]) and int(n1[0]) == int(nx[b])):
+            differ.append((b, int(kv_len[b])))
+    assert not differ
     n = min(4, len(edges))
     lo = oracle.decode_step(hw.as_f32(), model, inputs.to_f32(dec.cache_k[:, :n]), inputs.to_f32(dec.cache_v[:, :n]),
                             dec.kv_len[:n], dec.token_ids[:n])[0]
