@@ -1338,7 +1338,7 @@ rp_status rp_calibrate_read(void* stream, const void* src, int64_t bytes, int32_
   return RP_OK;
 }
 
-// ---- for the tests: the form a launch would take (nothing is launched; not in rollplex.h) ----
+// ---- for the tests (not in rollplex.h): the form a launch would take, and two forms of one step ----
 
 // Form (rp::GemmForm) and flexible tile of a GEMM.
 int32_t rp_test_gemm_form(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t trans, int32_t epi, int32_t splitk,
@@ -1365,6 +1365,27 @@ int32_t rp_test_suffix_chunks(const rp_model* m, int32_t n_prefix, const int32_t
   a.part_floats = (int64_t)w.plan.part_floats;
   const rp::AttnLongPlan p = rp::attn_long_plan(tab, a, scu[n_suffix]);
   return p.fold ? -p.chunks : p.S;
+}
+
+// A decode step's gate/up projection and SwiGLU on device buffers (x [M][K], weights [F][K], act
+// [M][F]): from split-K partials (partials holds M * 2 F floats per split), or, where partials is
+// NULL, with the chunks summed in the GEMM.  Returns the chunks, 0 where the form does not exist.
+int32_t rp_test_gate_up(void* stream, int32_t dtype, int32_t M, int32_t F, int32_t K, const void* x, const void* w_gate,
+                        const void* w_up, float* partials, void* act) {
+  const rp_dtype dt = (rp_dtype)dtype;
+  hipStream_t s = (hipStream_t)stream;
+  if (dt == RP_F32 || M < 1 || M > 64 || F < 64 || F % 64 || K < 64 || K % 64) return 0;
+  const int splitk = rp::gemm_skinny_splitk(M, 2 * F, K);
+  const rp::BSeg b = {w_gate, w_up, w_up, F, 2 * F};
+  if (!partials) {
+    if (!rp::gemm_swiglu_chunks(dt, M, F, K, splitk)) return 0;
+    if (rp::launch_gemm(s, dt, M, F, K, x, K, b, K, act, F, rp::EPI_SWIGLU, splitk, nullptr) != hipSuccess) return 0;
+  } else {
+    if (rp::launch_gemm(s, dt, M, 2 * F, K, x, K, b, K, nullptr, 2 * F, rp::EPI_PARTIALS, splitk, partials) != hipSuccess ||
+        rp::launch_splitk_swiglu(s, dt, partials, rp::gemm_effective_splitk(dt, K, splitk), M, F, act) != hipSuccess)
+      return 0;
+  }
+  return rp::gemm_effective_splitk(dt, K, splitk);
 }
 
 int rp_device_cu_count(int device) {
