@@ -562,7 +562,9 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(SeqTable st, AttnArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  // Lowest number, not -inf: a tile whose scores are all -inf must leave the weights numbers, and
+  // its wave a sum of 0, where other waves hold the other keys.
+  float m = -3.4028235e38f, l = 0.f;
   if (wave < ntiles) load_k(wave);
   for (int t = wave; t < ntiles; t += NW) {
     const float *kb, *vb;

@@ -1,6 +1,6 @@
 """The fp32 matrix-core kernels at their edges: tiles of 32 rows, keys and columns, K that is
 no multiple of the 32-deep loads (8-deep chunks split over four waves), head_dim 128, and
-non-finite values of later tokens, which must not reach earlier ones."""
+non-finite values of later tokens, which must not reach earlier ones, and scores of -inf."""
 import numpy as np
 import pytest
 import torch
@@ -64,4 +64,37 @@ def test_f32_non_finite_token_leaves_earlier_rows(model, at):
         assert torch.isfinite(b).all()
         assert float((a - b).abs().max() / a.abs().max()) <= 1e-5
     assert not torch.isfinite(xb[at:]).any()
+    dm.close()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("first,last", [(32, 64), (32, 95), (64, 300), (1, 301)])
+def test_f32_keys_of_score_minus_infinity_weigh_nothing(head_dim, first, last):
+    """Prefix keys first .. last - 1 hold -inf in the dimension of the slowest rotation, where every
+    query is positive: their scores are -inf, whole 32-key tiles of them, and the result is that of
+    scores of -1e30."""
+    n = 301
+    model = configs.ModelShape(n_layers=1, d_model=72, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, ffn_dim=40,
+                               vocab=101, dtype="f32")
+    w = configs.custom(model, [n], [0], [33], index=87)
+    hw = inputs.make_weights(w, norm="random", bias=True)
+    lw = hw.layers[0]
+    dim = head_dim // 2 - 1  # rotates by n theta^(2 / D - 1): 5e-4 at most
+    for h in range(2):
+        r = h * head_dim + np.array([dim, dim + head_dim // 2])
+        lw["wq"][r] = 0
+        lw["bq"][r] = [1, 0]
+    bt = inputs.make_batch(w)
+    dm = DeviceModel(hw, 512)
+    K, V, hl = dm.prefix([0, n], to_device(bt.token_ids, dm.device), None)
+
+    def run(value):
+        k = K.clone()
+        k[:, first:last, :, dim] = value
+        return dm.suffix([0, n], [0, 33], k, V, hl, to_device(bt.response_ids, dm.device))
+
+    want, got = run(-1e30), run(float("-inf"))
+    assert torch.isfinite(want).all()
+    # fp32 sums of at most 334 terms, in the same order (keys of weight 0 add zeros)
+    assert torch.equal(want, got)
     dm.close()
