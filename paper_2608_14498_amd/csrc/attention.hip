@@ -22,6 +22,8 @@
 #include "device_common.h"
 #include "rp_internal.h"
 
+#include <math.h>
+
 #include <type_traits>
 
 namespace rp {
@@ -747,17 +749,50 @@ static bool attn_wide(const SeqTable& st) {
   return max_q >= 8192;
 }
 
-// The chunks go to workgroups of their own while the blocks alone leave CUs short of the two
-// workgroups that they hold and the partials fit the scratch memory at hand.
+// Rounds that x times as many equal workgroups take as the CUs hold two of: a last round of one
+// workgroup a CU takes little over half of a full one, and after a few rounds the workgroups have
+// drifted apart and end evenly.
+static double attn_rounds(double x) {
+  const double full = floor(x + 1e-6), rem = x - full;
+  if (rem < 1e-6) return full;
+  const double last = rem <= 0.5 ? 0.5 + 0.3 * rem : std::min(1., 0.65 + 0.37 * rem);
+  return full + rem + (last - rem) * (full <= 1. ? 1. : 1.5 / full);
+}
+
+// Chunks on workgroups of their own (S slots, then a merge), or all chunks of a block in one?
+// Cut, the last round of workgroups is shorter and few blocks reach more CUs; whole, nothing is
+// written and a block's tiles follow each other.  Both give the same bits, so the whole batch
+// decides: two workgroups a CU (one of 8 waves), 32 ns a key and round of them (19.5 with
+// D = 64), 4 us a workgroup, the partials' bytes at 6 TB/s (some of them move under the tiles),
+// 4 us for the merge.  Over 1124 batches (1 to 3500 blocks, 512 to 32768 keys, 6 to 40 heads) the
+// choice costs 0.6% over the better form on average, 29% at most, where "cut below 512 blocks"
+// cost 5.7% and 136%.  us, whole / cut: 8 responses of 700 tokens over 16384 keys, 12 heads (528
+// blocks) 881 / 654, of 1000 969 / 898; 64 of 128 over 1024 keys, 6 heads (384 blocks) 56 / 102;
+// 128 of 40 over 4096, 28 heads (1536 blocks) 482 / 695; 48 tokens over 1501, 28 heads 36 / 23.
 AttnLongPlan attn_long_plan(const SeqTable& st, const AttnArgs& a, int32_t total_q) {
   AttnLongPlan p;
   p.wide = attn_wide(st);
-  p.grid = fa_grid(fa_map(a.Hkv, a.Hkv), count_qblocks(st, p.wide ? 256 : 128, a.Hq / a.Hkv), a.Hkv);
+  const int BQ = p.wide ? 256 : 128, P = a.Hq / a.Hkv;
+  p.grid = fa_grid(fa_map(a.Hkv, a.Hkv), count_qblocks(st, BQ, P), a.Hkv);
   p.chunks = 1;
-  for (int b = 0; b < st.n; ++b)
-    p.chunks = std::max(p.chunks, attn_chunks(st.pos0(b), st.q_cu[b + 1] - st.q_cu[b], a.Hq, a.Hkv, a.most_chunks));
+  const double slots = p.wide ? 256. : 512., key = a.D == 128 ? 0.032 : 0.0195, start = 4.;
+  double whole = 0., cut = 0., bytes = 0.;                  // us of all workgroups
+  double longest_whole = start, longest_cut = start;        // and of the longest one
+  for (int b = 0; b < st.n; ++b) {
+    const int n0 = st.pos0(b), nq = st.q_cu[b + 1] - st.q_cu[b];
+    if (nq <= 0) continue;
+    const int c = attn_chunks(n0, nq, a.Hq, a.Hkv, a.most_chunks);
+    p.chunks = std::max(p.chunks, c);
+    const double blocks = (double)(((int64_t)nq * P + BQ - 1) / BQ) * a.Hkv, work = key * (n0 + 0.5 * nq);
+    whole += blocks * (work + start);
+    cut += blocks * (work + start * c);
+    longest_whole = std::max(longest_whole, work + start);
+    longest_cut = std::max(longest_cut, work / c + start);
+    if (c > 1) bytes += (double)nq * a.Hq * c * (a.D + 2) * 4.;
+  }
   const bool fit = a.part && (int64_t)attn_partial_floats(total_q, a.Hq, a.D, p.chunks) <= a.part_floats;
-  p.fold = p.chunks > 1 && (p.grid >= 512 || !fit);
+  p.fold = p.chunks > 1 && (!fit || attn_rounds(whole / longest_whole / slots) * longest_whole <=
+                                        attn_rounds(cut / longest_cut / slots) * longest_cut + bytes / 6e6 + 4.);
   p.S = p.fold ? 1 : p.chunks;
   return p;
 }

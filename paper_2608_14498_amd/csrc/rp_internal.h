@@ -225,7 +225,8 @@ __host__ __device__ inline int attn_splits(int n0) {
 // Key chunks of a sequence of nq queries over n0 first-segment keys: a function of the sequence
 // and the model (head counts, most) alone, so its result does not depend on the sequences packed
 // with it.  As many as bring the sequence to about 64 workgroups, of 256 keys or more: 48 queries
-// over 1501 keys (7B heads) run 36 -> 23 us a layer.  Aiming at 128 cut 4 responses of 256 tokens
+// over 1501 keys (7B heads) run 36 -> 23 us a layer.  Fewer than 1024 keys stay whole (48 queries
+// over 512, 40 heads: 19 us, and 20 to 23 in two chunks).  Aiming at 128 cut 4 responses of 256 tokens
 // in two and left them at 100 us (two workgroups on a CU each run at little over half speed).
 // At most `most` (up to kAttnMostChunks), but long segments are cut whatever the queries.
 constexpr int kAttnMostChunks = 7;
@@ -233,7 +234,7 @@ __host__ __device__ inline int attn_chunks(int n0, int nq, int Hq, int Hkv, int 
   if (nq <= 0) return 1;  // an empty response
   const int blocks = (nq * (Hq / Hkv) + 127) / 128 * Hkv;
   int c = (64 + blocks / 2) / blocks;
-  c = c < n0 / 256 ? c : n0 / 256;
+  c = n0 < 1024 ? 1 : c < n0 / 256 ? c : n0 / 256;
   c = c < most ? c : most;
   const int least = attn_splits(n0);
   return c > least ? c : least;

@@ -15,17 +15,20 @@ SMALL64 = replace(SMALL, n_q_heads=8, n_kv_heads=2, head_dim=64, ffn_dim=1024, d
 TWO_WAYS = replace(SMALL, ffn_dim=2048)  # a down projection in two K splits
 
 
-def suffix_chunks(handle, prefix, lens):
-    """Key-chunk slots of the suffix attention of responses `lens` over one prefix (negative: a
-    workgroup takes all chunks)."""
+def suffix_chunks(handle, prefix, lens, of=None):
+    """Key-chunk slots of the suffix attention of responses `lens` over one prefix, or over prefixes
+    `prefix` [of[i]] (negative: a workgroup takes all chunks)."""
     arr = lambda v: (ctypes.c_int32 * len(v))(*v)
     f = rb.lib().rp_test_suffix_chunks
     f.restype = ctypes.c_int32
     f.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
-    cu = [0]
-    for n in lens:
-        cu.append(cu[-1] + n)
-    return f(handle, 1, arr([0, prefix]), len(lens), arr([0] * len(lens)), arr(cu))
+    cums = []
+    for sizes in ([prefix] if of is None else prefix, lens):
+        cu = [0]
+        for n in sizes:
+            cu.append(cu[-1] + n)
+        cums.append(arr(cu))
+    return f(handle, len(cums[0]) - 1, cums[0], len(lens), arr(of or [0] * len(lens)), cums[1])
 
 
 @pytest.mark.parametrize("model", [SMALL, SMALL64, TWO_WAYS, configs.QWEN7B_SLICE, configs.QWEN32B_SLICE])
@@ -38,6 +41,39 @@ def test_a_lone_response_spreads_a_long_prefix_over_workgroups(model):
             for n in (1, 48, 64, 300, 900):
                 got = suffix_chunks(h, prefix, [n])
                 assert got >= max(1, min(8, prefix // 4096)), (prefix, n, got)
+    finally:
+        rb.rp_destroy(h)
+
+
+def _heads(hq, hkv, d_model, ffn, head_dim=128, dtype="bf16"):
+    return replace(SMALL, n_layers=1, n_q_heads=hq, n_kv_heads=hkv, d_model=d_model, ffn_dim=ffn, head_dim=head_dim,
+                   dtype=dtype)
+
+
+SIX, TWELVE, WIDE, HALF = (_heads(6, 3, 1024, 8192), _heads(12, 2, 1024, 8192), _heads(28, 4, 3584, 18944),
+                           _heads(16, 2, 1024, 8192, 64, "f16"))
+
+
+# batches whose two forms differ by a fifth and more: us of the attention, one workgroup for all
+# chunks / a workgroup for each
+@pytest.mark.parametrize("model,prefix,lens,whole", [
+    (TWELVE, 16384, [700] * 8, False),    # 881 / 654: 528 blocks, a second round of 16
+    (TWELVE, 32768, [1400] * 8, False),   # 2803 / 2398
+    (TWELVE, 16384, [3000] * 2, False),   # 913 / 708
+    (WIDE, 16384, [300] * 8, False),      # 885 / 655
+    (WIDE, 1500, [48], False),            # 36 / 23
+    (HALF, 32768, [300] * 8, False),      # 628 / 462
+    (SIX, 1024, [128] * 64, True),        # 56 / 102: 384 blocks
+    (SIX, 1024, [200] * 40, True),        # 57 / 109
+    (HALF, 1024, [128] * 16, True),       # 27 / 49
+    (TWELVE, 1024, [40] * 128, True),     # 63 / 141
+    (WIDE, 4096, [40] * 128, True),       # 482 / 695
+    (HALF, 8192, [40] * 128, True)])      # 298 / 411
+def test_chunks_take_the_faster_form(model, prefix, lens, whole):
+    h, keep = make(model, 60000)
+    try:
+        got = suffix_chunks(h, prefix, lens)
+        assert abs(got) > 1 and (got < 0) == whole, got
     finally:
         rb.rp_destroy(h)
 

@@ -1,7 +1,7 @@
 """Attention over a long first key segment in key chunks: a response alone (its chunks on
 workgroups of their own, then merged) must give bitwise what it gives in a batch whose blocks
 fill the chip (all chunks in one workgroup).  Parity with the oracle is the other tests'.  Response
-lengths sit on the edges of the chunk rule (blocks of 128 packed rows, chunks of 256 keys) and
+lengths sit on the edges of the chunk rule (blocks of 128 packed rows, chunks of 256 keys, 1024 keys and more cut) and
 of the 4- and 8-wave blocks.  The library is asked which form each launch takes, so that the two
 sides of a comparison are known to differ."""
 from dataclasses import replace
@@ -25,15 +25,15 @@ FIVE_CHUNKS = replace(WIDE_HEADS, d_model=512, dtype="f16")  # memory for 5
 
 
 @pytest.mark.parametrize("model,prefix,lens,fill", [
-    (MODEL, [511, 512, 1501, 8192], [1, 16, 17, 32, 33, 48, 64, 65, 96, 97, 129, 300], 256),
+    (MODEL, [512, 1023, 1024, 1501, 8192], [1, 16, 17, 32, 33, 48, 64, 65, 96, 97, 129, 300], 256),
     (F16, [8192, 1501], [16, 48, 129, 300], 256),
-    (WIDE_HEADS, [2047, 257], [1, 42, 43, 64, 85, 200], 200),
-    (replace(WIDE_HEADS, dtype="f16"), [8192, 1501], [1, 42, 43, 64, 85, 200], 200),
-    (FIVE_CHUNKS, [2047, 257], [1, 42, 43, 64, 85, 200], 200),
-    (MODEL, [1793, 600], [8200, 31, 64], 6)])
+    (WIDE_HEADS, [2047, 1025], [1, 42, 43, 64, 85, 200], 200),
+    (replace(WIDE_HEADS, dtype="f16"), [8192, 1501], [1, 42, 43, 64, 85, 200], 250),
+    (FIVE_CHUNKS, [2047, 1025], [1, 42, 43, 64, 85, 200], 200),
+    (MODEL, [1793, 1100], [8200, 31, 64], 6)])
 def test_chunks_alone_and_in_a_batch(model, prefix, lens, fill):
-    """fill: responses in the batch; 256 of one block over 2 kv heads are the 512 blocks from
-    which a workgroup takes all chunks.  The 8200-token responses put theirs in 8-wave blocks."""
+    """fill: responses in the batch, enough of them that a workgroup takes all chunks.  The
+    8200-token responses put theirs in 8-wave blocks."""
     w = configs.custom(model, [1], [0], [0], index=85)
     dm = DeviceModel(inputs.make_weights(w, norm="random", bias=True), max(prefix) + max(lens) + 1)
     g = torch.Generator(device="cuda").manual_seed(3)
@@ -47,8 +47,7 @@ def test_chunks_alone_and_in_a_batch(model, prefix, lens, fill):
     of = sorted(int(x) for x in rng.integers(0, len(prefix), fill))
     ids = [rng.integers(0, model.vocab, n, dtype=np.int32) for n in want]
     scu = [0] + [int(x) for x in np.cumsum(want)]
-    for p in range(len(prefix)):  # the whole batch over one prefix: one workgroup takes all chunks
-        assert suffix_chunks(dm.handle, prefix[p], want) < 0 or prefix[p] < 512, prefix[p]
+    assert suffix_chunks(dm.handle, prefix, want, of) < 0  # one workgroup takes all chunks
     whole = dm.suffix_grouped(pcu, of, scu, K, V, h, to_device(np.concatenate(ids), dm.device))
     assert torch.isfinite(whole).all()
     seen, split = set(), 0
