@@ -1367,6 +1367,13 @@ int32_t rp_test_suffix_chunks(const rp_model* m, int32_t n_prefix, const int32_t
   return p.fold ? -p.chunks : p.S;
 }
 
+// 1 where a decode step's attention runs one wave per key chunk.
+int32_t rp_test_decode_deep(const rp_model* m, int32_t B, int32_t cap) {
+  const rp_config& c = m->cfg;
+  return half_dtype(c) && rp::decode_attn_deep(B, c.n_q_heads, c.n_kv_heads, c.head_dim, cap,
+                                               (int64_t)B * (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim);
+}
+
 // A decode step's gate/up projection and SwiGLU on device buffers (x [M][K], weights [F][K], act
 // [M][F]): from split-K partials (partials holds M * 2 F floats per split), or, where partials is
 // NULL, with the chunks summed in the GEMM.  Returns the chunks, 0 where the form does not exist.

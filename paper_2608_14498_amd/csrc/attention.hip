@@ -1505,6 +1505,17 @@ size_t decode_attn_partial_floats(int32_t B, int32_t Hq, int32_t D, int32_t cap)
   return (size_t)B * Hq * nchunks * (D + 2);
 }
 
+// One wave per chunk where each can have a compute unit to itself (and the records fit).  Up to
+// three chunks are one record of the three-wave form, which writes the result itself: without the
+// merge it is faster, unless three full chunks of rows of 1 KB and more share a CU.  us with
+// launches and timing events, a wave per chunk / three waves: 998 keys, 2 kv heads of 128, 64
+// sequences 33 / 27; 2046 keys 34 / 30; 3070 keys 33 / 30, but 33 / 43 with 4 kv heads.
+bool decode_attn_deep(int32_t B, int32_t Hq, int32_t Hkv, int32_t D, int32_t cap, int64_t sums_floats) {
+  const int nchunks = (cap + DC_KEYS - 1) / DC_KEYS;
+  return (nchunks > 3 || (nchunks == 3 && Hkv * D >= 512)) && (int64_t)B * Hkv * nchunks <= 256 &&
+         decode_groups(nchunks) <= 64 && (int64_t)B * Hq * nchunks * 4 <= sums_floats;
+}
+
 hipError_t launch_decode_attention(hipStream_t s, rp_dtype dt, const void* q, int32_t q_ld,
                                    const void* cache_k, const void* cache_v, const int32_t* kv_len,
                                    int32_t cap, int32_t max_pos, int32_t B, int32_t Hq, int32_t Hkv,
@@ -1531,9 +1542,7 @@ hipError_t launch_decode_attention(hipStream_t s, rp_dtype dt, const void* q, in
   // the 16-bit kernel addresses a sequence's cache rows with 32-bit byte offsets
   if ((int64_t)cap * Hkv * D * 2 > (int64_t)INT32_MAX) return hipErrorInvalidValue;
   const int nrec = decode_groups(nchunks);
-  // One wave per chunk where each can have a compute unit to itself (and the records fit).
-  const bool deep = (int64_t)B * Hkv * nchunks <= 256 && nrec <= 64 && sums && !((uintptr_t)sums & 15) &&
-                    (int64_t)B * Hq * nchunks * 4 <= sums_floats;
+  const bool deep = decode_attn_deep(B, Hq, Hkv, D, cap, sums_floats) && sums && !((uintptr_t)sums & 15);
   const int grid = B * Hkv * (deep ? nchunks : nrec), mgrid = (B * Hq + 3) / 4;
   with_half16(dt, [&](auto tag_) {
     using H = decltype(tag_);

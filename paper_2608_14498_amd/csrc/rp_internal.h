@@ -305,6 +305,8 @@ hipError_t launch_rope_kv_splitk(hipStream_t s, rp_dtype dt, const SeqTable& st,
 // X[b] = E[ids[b]] (clamped); out[b] = RMSNorm(X[b]) * w.
 hipError_t launch_decode_embed_norm(hipStream_t s, rp_dtype dt, const int32_t* ids, const void* embed, int32_t vocab,
                                     int32_t B, int32_t d, float* X, const void* w, float eps, void* out);
+// Whether the 16-bit decode attention runs one wave per key chunk (given aligned scratch).
+bool decode_attn_deep(int32_t B, int32_t Hq, int32_t Hkv, int32_t D, int32_t cap, int64_t sums_floats);
 // partials: decode_attn_partial_floats; sums: further scratch (sums_floats floats, 16-byte
 // aligned, may be none) that lets few sequences run one wave per chunk.
 hipError_t launch_decode_attention(hipStream_t s, rp_dtype dt, const void* q, int32_t q_ld,

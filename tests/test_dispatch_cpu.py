@@ -111,3 +111,23 @@ def test_a_row_tail_does_not_read_the_lm_head_again(model, epi):
     took 3 to 6% longer than the launch left whole (772 to 926 rows, 7B)."""
     for rows in range(65, 4000, 3):
         assert gemm_form("bf16", rows, model.vocab, model.d_model, epi)[0] != "cut rows", rows
+
+
+def decode_deep(handle, batch, cap):
+    """Whether a decode step's attention runs one wave per 1024-key chunk."""
+    f = rb.lib().rp_test_decode_deep
+    f.restype, f.argtypes = ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32]
+    return bool(f(handle, batch, cap))
+
+
+@pytest.mark.parametrize("model,batch,cap,deep", [
+    (TWELVE, 64, 1000, False), (TWELVE, 1, 200, False),  # one record: no merge where it is written directly
+    (WIDE, 16, 1100, False), (WIDE, 32, 2048, False), (TWELVE, 32, 3072, False), (HALF, 16, 3072, False),
+    (WIDE, 16, 3072, True), (WIDE, 1, 4000, True), (TWELVE, 16, 6000, True), (HALF, 4, 9000, True),
+    (WIDE, 64, 4000, False)])  # more chunks than compute units
+def test_decode_attention_takes_the_faster_form(model, batch, cap, deep):
+    h, keep = make(model, 60000)
+    try:
+        assert decode_deep(h, batch, cap) == deep
+    finally:
+        rb.rp_destroy(h)

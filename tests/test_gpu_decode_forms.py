@@ -16,12 +16,13 @@ from paper_2608_14498_amd import binding as rb
 from paper_2608_14498_amd import configs, inputs
 from paper_2608_14498_amd.runtime import DeviceModel, to_device
 from tests.gpu_helpers import max_abs
+from tests.test_dispatch_cpu import decode_deep
 
 pytestmark = pytest.mark.gpu
 
 WIDE_F = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=4, head_dim=128, ffn_dim=12800,
                             vocab=1003, dtype="bf16")
-F16_D64 = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=16, n_kv_heads=2, head_dim=64, ffn_dim=512,
+F16_D64 = configs.ModelShape(n_layers=2, d_model=256, n_q_heads=16, n_kv_heads=8, head_dim=64, ffn_dim=512,
                              vocab=1003, dtype="f16")
 
 
@@ -46,6 +47,7 @@ def test_alone_and_in_a_batch_the_same_bits(model, cap, edges, alone):
                         ids[rows].contiguous(), logits=logits)
         return logits, nxt
 
+    assert decode_deep(dm.handle, 1, cap) and not decode_deep(dm.handle, B, cap)
     lg, nx = step(list(range(B)))
     assert torch.isfinite(lg).all()
     assert torch.equal(nx.long(), lg.argmax(1))
