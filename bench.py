@@ -9,7 +9,10 @@ batch 2, prefix 16384 (15872 visual + 512 text), suffix 512.  The default run
 also reports the 7B-slice workloads (uniform and ragged batches) under
 "workloads" and the co-location arms of Eq. (1) under "colocation".
 
-Prints ONE JSON line on stdout; progress goes to stderr.
+Prints ONE JSON line on stdout; progress goes to stderr.  The line holds what is read off it
+(the headline record, its variants and rooflines, the other workloads' throughputs) in a few
+kilobytes, so that a log's tail keeps it whole; --details FILE writes every measurement
+(per-kernel times, every co-location arm).
 """
 from __future__ import annotations
 
@@ -267,6 +270,8 @@ def main():
                     help="skip timing the prompt-token log-probs (rp_prompt_logprob)")
     ap.add_argument("--no-extra-workloads", action="store_true",
                     help="report the named workload only (no 7B-slice workloads, no co-location arms)")
+    ap.add_argument("--details", default="", metavar="FILE",
+                    help="also write the whole record (per-kernel times, every arm) to FILE")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MIB",
                     help="only run a plain device-to-device copy of MIB MiB (counter calibration)")
     args = ap.parse_args()
@@ -292,7 +297,7 @@ def main():
     if args.dtype:
         w = configs.with_model(w, dtype=args.dtype)
     if w.decode is not None:
-        print(json.dumps(colocation(args, w)), flush=True)
+        emit(colocation(args, w), args)
         return
     out = workload_record(w, args, headline=True)
     if not args.no_extra_workloads and args.workload == HEADLINE and not args.dtype:
@@ -300,7 +305,34 @@ def main():
         for name in EXTRA_WORKLOADS:
             out["workloads"][name] = workload_record(configs.get(name), args, headline=False)
         out["colocation"] = colocation(args, configs.get(COLOCATION))
-    print(json.dumps(out), flush=True)
+    emit(out, args)
+
+
+def emit(out: dict, args):
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(brief(out)), flush=True)
+
+
+# what the line leaves out of every record, and of the records within the headline's
+DETAIL = {"kernels", "decode_kernels", "arms", "algorithmic_per_unit", "mfma_probe", "read_probe"}
+REPEATED = {"metric", "unit", "n_gpus", "steps", "warmup", "higher_is_better", "scaling", "vs_baseline", "data",
+            "config", "step_ms", "label"}
+
+
+def brief(rec, top: bool = True):
+    """The record without its details, floats to six digits."""
+    if isinstance(rec, float):
+        return float(f"{rec:.6g}")
+    if not isinstance(rec, dict):
+        return rec
+    out = {k: v for k, v in rec.items() if k not in DETAIL and (top or k not in REPEATED)}
+    for k in ("workloads", "colocation", "fused_logprob_variant", "f16_variant", "transposed_weights_variant",
+              "last_rows_only_variant"):
+        if k in out:
+            out[k] = ({n: brief(r, False) for n, r in out[k].items()} if k == "workloads" else brief(out[k], False))
+    return {k: brief(v) if isinstance(v, (dict, float)) else v for k, v in out.items()}
 
 
 def workload_record(w, args, headline: bool) -> dict:
