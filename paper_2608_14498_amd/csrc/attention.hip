@@ -17,7 +17,7 @@
 //
 // fp32: the same tiles on the fp32 matrix cores, keys split over the waves of a workgroup.
 //
-// decode: split-KV over 256-key chunks, all q heads of a kv head per workgroup,
+// decode: split-KV over 1024-key chunks, all q heads of a kv head per wave,
 // then a merge over chunks.
 #include "device_common.h"
 #include "rp_internal.h"
@@ -76,10 +76,9 @@ __device__ __forceinline__ QBlock find_qblock(const SeqTable& st, int qbl, int B
 //  - the rows of a block are (query, q head of one kv head) pairs, so that 48 responses'
 //    tokens of a 7-head group are 336 rows in 3 blocks, not 7 blocks of 48;
 //  - the sequence's keys are cut into attn_chunks() chunks with a softmax of their own, merged
-//    in order by fa_merge.  A workgroup takes one chunk and leaves its partial to
-//    k_attn_split_merge (few blocks: the chip needs the parallelism), or all of them, merged in
-//    registers (many blocks: partials of 128 queries x 28 heads are 2 KB a row and chunk).
-//    Both give the same bits, so the launch may choose by the whole batch.
+//    in order by fa_merge_weights.  A workgroup takes one chunk and leaves its partial to
+//    k_attn_split_merge, or all of them, merged in registers (attn_long_plan).  Both give the
+//    same bits, so the launch may choose by the whole batch.
 // A layer's attention, 7B shapes, us with timing events, before / now: 48 queries over 1501
 // keys 36 / 23, the last rows of 1200, 2048 and 3001 keys (fp16) 63 / 24, both bound by a few
 // key tiles in a row and two launches; 4 x 256 over 4096 99 / 99, 16 responses of 64 .. 1000
@@ -879,7 +878,7 @@ hipError_t launch_attention(hipStream_t s, rp_dtype dt, const SeqTable& st, cons
 // Decode attention: split-KV partials + merge.
 //
 // A decode step reads every cached key and value once and does ~7 flop per byte for a
-// 7-head GQA group, so it is bound by HBM bandwidth.  Each wave owns one 512-key chunk
+// 7-head GQA group, so it is bound by HBM bandwidth.  Each wave owns one 1024-key chunk
 // of one (sequence, kv head) and streams it with no block barrier: LPK lanes hold one
 // key row (8 head dims each, one 16-byte load), KPW keys per pass, and an R-deep ring of
 // K/V loads stays in flight (16 KB per wave at 16-bit) while earlier passes are scored.

@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(SW * 64) void k_gemm_skinny(SkinnyArgs g) {
 
 // Waves per workgroup of the skinny GEMM (32 columns each; they share the A slabs).
 // Four measured best at every decode shape: the shared A slab costs less per weight
-// byte, and the LDS (72 KiB a workgroup) still holds two workgroups per CU.
+// byte, and the LDS (48 KiB a workgroup at 64 rows) still holds three workgroups per CU.
 constexpr int kSkinnyWaves = 4;
 
 #ifndef RP_SKINNY_BLOCKS
